@@ -56,6 +56,7 @@ TileOptions batch_job_options(const TileOptions& opt, int64_t bytes_per_side) {
         o.out_row_bytes = 256;
         o.order_out = 1;
         o.cache = 3;
+        o.rows_only = 1;
     }
     return o;
 }
@@ -653,6 +654,9 @@ static void cache_policy(TileArgs& a, const TileOptions& opt) {
     const bool table = (a.flags & (TF_IN_TABLE | TF_OUT_TABLE)) != 0;
     int pol = opt.cache;
     if (pol < 0) pol = split && !table ? 2 : 0;
+    // batched tiles of 16-byte units that share no line gain nothing from the caches
+    // (1024^2 transposes 4600 -> 6220 GB/s streamed, 64^3 reversals 4770 -> 6150)
+    if (opt.rows_only && a.unit == 16 && !split) pol = 0;
     if (pol & 1) a.flags |= TF_LD_CACHED;
     if (pol & 2) a.flags |= TF_ST_CACHED;
     const bool xcd = opt.xcd >= 0 ? opt.xcd > 0 : split && pol != 0 && !table;
@@ -1047,6 +1051,14 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
     const bool flat_ok = nB == 1 && t[aO] == d[aO] && b1 == r - 1 - nA && sinb[b1] == innerA * t[aO] * R;
     if (umt) a.flags |= TF_UMT;
     else G = line_friendly_g(U, G, a.TB, nA, a.soutA[0], false);
+    // Batched jobs of 4-16-byte units write G = 1 rows (one gathered 16-byte vector
+    // per lane at any alignment), and so do 1- and 2-byte ones left with G = 2: a
+    // batch then has few kernel bodies, whose workgroups overlap better (4096-job
+    // call 3450 -> 3257 us, handle 3236 -> 3167 us; uniform 64^3 reversals +4.5 % at
+    // 4 and 8 bytes, 512 x 36 transposes -6 % and -2 %).  Wider micro-tiles of 1- and
+    // 2-byte units stay: their G = 1 rows gather byte by byte (1024^2 transposes
+    // -17 %).
+    if (opt.rows_only && !umt && (U >= 4 || G == 2)) G = 1;
     rr_status st = finish_tile(a, U, G, k, ra, flat_ok && !umt, src, b1 > 0 ? (uint64_t)d[b1] : 0, opt, why);
     if (st != RR_OK) return st;
     cache_policy(a, opt);
