@@ -185,7 +185,10 @@ rr_status rr_deinterlace(void* const* dsts, const void* src, int n, int64_t coun
  * The job table is staged through pinned host and device buffers the library
  * owns (a small ring per device, grown on demand and held until process exit);
  * a call waits only if it would reuse a slot whose batch is still running.
- * The groups run side by side on `stream` and three side streams per device
+ * A batch of at most 512 MiB per side goes out as one launch over its groups on
+ * `stream` (groups of tiles above 16 KiB, or of shapes that only a tile override
+ * or a tuned cache entry plans, keep launches of their own).  Several launches
+ * run side by side on `stream` and three side streams per device
  * that the library owns (default priority, held until process exit): they start
  * after the work queued on `stream` before the call, and work queued on `stream`
  * after the call waits for all of them.  Calls on one device share those side
@@ -241,7 +244,9 @@ rr_status rr_permute_batched_noalloc(const rr_job* jobs, int njobs, rr_stream_t 
  * Reusable batch: validate, plan and group the jobs once, keep the job table
  * resident in device memory owned by the handle, launch many times.
  *   flags  RR_BATCH_GRAPH      launches replay a hipGraph captured on the
- *                              first rr_batch_launch (one graph launch per call);
+ *                              first rr_batch_launch (one graph launch per call;
+ *                              a batch that is a single launch is launched
+ *                              directly instead);
  *          RR_BATCH_TUNE       rr_batch_create times candidate tile shapes and
  *                              grid modes (running the batch, so it writes the
  *                              job outputs) on the current device and keeps the
@@ -258,7 +263,9 @@ rr_status rr_permute_batched_noalloc(const rr_job* jobs, int njobs, rr_stream_t 
  *                              kernel time can then be read on its own.
  * Jobs are planned like rr_permute (the tile override if one is set, else the
  * built-in shapes and the tuning cache).  The handle's device is the current
- * HIP device at creation.  A launch runs its groups side by side on `stream`
+ * HIP device at creation.  A batch of at most 512 MiB per side is launched as
+ * rr_permute_batched launches one (persistent and serial handles excepted);
+ * a larger one runs its groups side by side on `stream`
  * and three streams the handle owns (default priority): they start after the
  * work queued on `stream` before the call, and work queued on `stream` after
  * the call waits for all of them.  Launches on different streams must not
@@ -275,8 +282,8 @@ typedef struct rr_batch rr_batch;
 
 typedef struct {
     int32_t njobs;             /* jobs with a non-empty problem                */
-    int32_t ngroups;           /* groups (kernel family x LDS size class) =
-                                  launches per batch                           */
+    int32_t ngroups;           /* groups (kernel family x LDS size class); a
+                                  small batch runs most of them in one launch  */
     int32_t in_row_bytes;      /* tile shape chosen (0 = built-in)              */
     int32_t out_row_bytes;
     int32_t order_out;         /* tile traversal in output order                */

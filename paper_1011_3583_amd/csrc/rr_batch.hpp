@@ -68,6 +68,35 @@ struct BatchPlan {
     uint32_t njobs = 0;
 };
 
+// One launch over several groups of a batch: the groups' workgroups laid end to
+// end.  A group's `code` names the kernel body its workgroups run: W for copies of
+// W-byte vectors, FUSED_RUN + W for run copies, unit * 100 + g for tiles.  Offsets
+// are into the batch table.  The directory travels as a kernel argument, so a
+// workgroup finds its group by comparing scalars.
+constexpr uint32_t FUSED_RUN = 32;
+constexpr int FUSED_MAX_GROUPS = 18;        // eight tile, five run and five copy bodies
+constexpr uint32_t FUSED_LDS_BYTES = 16384; // tile size class that may be fused
+struct FusedGroup {
+    uint32_t start;        // first workgroup of the launch that belongs to the group
+    uint32_t code;
+    uint32_t njobs;
+    uint32_t args_off;
+    uint32_t prefix_off;
+    uint32_t range_off;
+};
+struct FusedArgs {
+    uint64_t table;        // device address of the batch table
+    uint32_t ngroups;
+    uint32_t total;        // workgroups of the launch
+    uint32_t lds_bytes;    // largest tile of the fused groups
+    uint32_t pad_;
+    FusedGroup g[FUSED_MAX_GROUPS];
+};
+// Fill *out with the groups of p that one launch may cover, in launch order, and
+// mark them in *fused (one entry per group); the rest keep launches of their own.
+// Fewer than two such groups: none are marked (ngroups 0).
+void plan_fused(const BatchPlan& p, uint64_t table, FusedArgs* out, std::vector<uint8_t>* fused);
+
 // Validate and plan `njobs` jobs.  On error *bad_job is the index of the first
 // failing job (or -1 for a cross-job overlap) and nothing is planned.
 rr_status plan_batch(const rr_job* jobs, int njobs, const TileOptions& opt, BatchPlan* out,

@@ -375,4 +375,44 @@ rr_status build_batch(const std::vector<BatchEntry>& entries, BatchPlan* out, st
     return RR_OK;
 }
 
+// Tile bodies the fused kernel holds: those that batch_job_options plans.
+static bool fused_tile_variant(int v) { return v % 100 == 1 || v == 104 || v == 108 || v == 204; }
+
+// Tiles first: their workgroups live two to eight times as long as a copy or run
+// workgroup, so the short ones fill the chip while the last tiles finish.  Tiles
+// above 16 KiB would reserve their LDS for every workgroup of the launch and keep a
+// launch of their own, as do the micro-tiles that only overrides, tuned shapes and
+// jobs above BATCH_SMALL_JOB_BYTES plan.
+void plan_fused(const BatchPlan& p, uint64_t table, FusedArgs* out, std::vector<uint8_t>* fused) {
+    std::memset(out, 0, sizeof *out);
+    out->table = table;
+    fused->assign(p.groups.size(), 0);
+    uint64_t total = 0;
+    for (const int kind : {(int)K_TILE, (int)K_RUN, (int)K_COPY}) {
+        for (size_t i = 0; i < p.groups.size(); ++i) {
+            const BatchGroup& g = p.groups[i];
+            if (g.kind != kind || g.total_blocks == 0 || out->ngroups == (uint32_t)FUSED_MAX_GROUPS) continue;
+            if (kind == K_TILE && (g.lds_bytes > FUSED_LDS_BYTES || !fused_tile_variant(g.variant))) continue;
+            if (total + g.total_blocks > 0x7fffffffULL || std::max({g.args_off, g.prefix_off, g.range_off}) > 0xffffffffULL)
+                continue;
+            FusedGroup& f = out->g[out->ngroups++];
+            f.start = (uint32_t)total;
+            f.code = (uint32_t)g.variant + (kind == K_RUN ? FUSED_RUN : 0u);
+            f.njobs = g.njobs;
+            f.args_off = (uint32_t)g.args_off;
+            f.prefix_off = (uint32_t)g.prefix_off;
+            f.range_off = (uint32_t)g.range_off;
+            out->lds_bytes = std::max(out->lds_bytes, g.lds_bytes);
+            total += g.total_blocks;
+            (*fused)[i] = 1;
+        }
+    }
+    out->total = (uint32_t)total;
+    if (out->ngroups < 2) {
+        out->ngroups = 0;
+        out->total = 0;
+        fused->assign(p.groups.size(), 0);
+    }
+}
+
 }  // namespace rr

@@ -1620,6 +1620,17 @@ RR_HD uint32_t batch_block_to_tile(uint32_t flags, const EntryRange& r, uint32_t
     return batch_xcd_block(r, b);
 }
 
+// Group of workgroup b in a fused launch: the last one starting at or before b.
+// Every start is compared (starts past the last group are zeroed, so the count
+// is bounded by ngroups), in scalar registers.
+RR_HD uint32_t fused_group(const FusedArgs& f, uint32_t b) {
+    uint32_t k = 0;
+#pragma unroll
+    for (int i = 1; i < FUSED_MAX_GROUPS; ++i)
+        if ((uint32_t)i < f.ngroups && f.g[i].start <= b) k = (uint32_t)i;
+    return k;
+}
+
 template <int W>
 RR_HD void batch_copy_block(const CopyArgs* args, const uint32_t* prefix, const EntryRange* ranges,
                             uint32_t njobs, uint32_t b, uint32_t tid) {

@@ -41,10 +41,15 @@ struct GroupFanout {
 rr_status fanout_init(GroupFanout* f);
 void fanout_destroy(GroupFanout* f);
 
+// How the groups of a batch reach the device: fused (one launch over every group
+// that allows it, the rest on launches of their own), a launch per group, or a
+// launch per group of a persistent grid.
+enum class GroupLaunch { fused, each, persistent };
+
 // Launch every group of a batch whose table is resident at dev_table: one after
 // another on st, or (with a fanout) spread over st and the side streams, largest
-// groups first, each to the stream with the least work queued so far.
-rr_status launch_batch_plan(const BatchPlan& p, const uint8_t* dev_table, bool persistent, int device,
+// launches first, each to the stream with the least work queued so far.
+rr_status launch_batch_plan(const BatchPlan& p, const uint8_t* dev_table, GroupLaunch how, int device,
                             hipStream_t st, GroupFanout* fan = nullptr);
 
 }  // namespace rr

@@ -19,4 +19,7 @@ hipError_t launch_stencil(const StencilArgs& a, hipStream_t st);
 // block of work; a smaller grid makes the launch persistent (grid-stride).
 hipError_t launch_batch_group(const BatchGroup& g, const uint8_t* table, uint32_t grid, hipStream_t st);
 
+// Enqueue one launch over the groups of a batch listed in f (f.total > 0).
+hipError_t launch_batch_fused(const FusedArgs& f, hipStream_t st);
+
 }  // namespace rr

@@ -75,5 +75,5 @@ extern "C" rr_status rr_permute_batched_noalloc(const rr_job* jobs, int njobs, r
     // the table) and has consumed the host buffer when it returns.
     e = hipMemcpyAsync(table, bp.table.data(), bp.table.size(), hipMemcpyHostToDevice, hs);
     if (e != hipSuccess) return hip_fail(e, "job table upload");
-    return launch_batch_plan(bp, (const uint8_t*)table, false, device, hs, nullptr);
+    return launch_batch_plan(bp, (const uint8_t*)table, GroupLaunch::fused, device, hs, nullptr);
 }

@@ -137,7 +137,7 @@ class HipBackend : public Backend {
         hipStream_t st = streams_[(size_t)stream];
         std::memcpy(s.host, bp.table.data(), need);
         hipError_t e = hipMemcpyAsync(s.dev, s.host, need, hipMemcpyHostToDevice, st);
-        rr_status rs = e == hipSuccess ? launch_batch_plan(bp, (const uint8_t*)s.dev, false, device_, st)
+        rr_status rs = e == hipSuccess ? launch_batch_plan(bp, (const uint8_t*)s.dev, GroupLaunch::fused, device_, st)
                                        : hip_fail(e, "server table upload");
         e = hipEventRecord(s.ev, st);
         if (rs == RR_OK && e != hipSuccess) rs = hip_fail(e, "hipEventRecord");

@@ -173,6 +173,38 @@ static bool emulate_group(const BatchGroup& g, const uint8_t* table) {
     return false;
 }
 
+// The fused launch's directory: its workgroups map one to one onto the workgroups
+// of the groups it covers, each with its group's body and table offsets.  Returns
+// the number of groups covered, -1 on a mismatch.
+static int check_fused(const BatchPlan& bp) {
+    FusedArgs f;
+    std::vector<uint8_t> in;
+    plan_fused(bp, 0, &f, &in);
+    std::vector<const BatchGroup*> by_start(f.ngroups, nullptr);
+    uint64_t covered = 0;
+    for (size_t i = 0; i < bp.groups.size(); ++i) {
+        if (!in[i]) continue;
+        const BatchGroup& g = bp.groups[i];
+        covered += g.total_blocks;
+        int hits = 0;
+        for (uint32_t k = 0; k < f.ngroups; ++k)
+            if (f.g[k].args_off == g.args_off && f.g[k].prefix_off == g.prefix_off && f.g[k].range_off == g.range_off &&
+                f.g[k].njobs == g.njobs && f.lds_bytes >= g.lds_bytes &&
+                f.g[k].code == (uint32_t)g.variant + (g.kind == K_RUN ? FUSED_RUN : 0u)) {
+                by_start[k] = &g;
+                ++hits;
+            }
+        if (hits != 1) return -1;
+    }
+    if (covered != f.total) return -1;
+    uint32_t k = 0, local = 0;
+    for (uint32_t b = 0; b < f.total; ++b, ++local) {
+        if (local == by_start[k]->total_blocks) { ++k; local = 0; }
+        if (fused_group(f, b) != k || b - f.g[k].start != local) return -1;
+    }
+    return (int)f.ngroups;
+}
+
 template <int R, int SHAPE, int TH>
 static void run_stencil_rs(const StencilArgs& a) {
     const size_t nl = (size_t)(TH + 2 * R) * ST_PITCH;
@@ -609,7 +641,8 @@ int main(int argc, char** argv) {
             } else if (differ) {
                 std::printf("err -3 %d concurrent plans differ\n", differ);
             } else {
-                bool ok = true;
+                const int nfused = check_fused(bp);
+                bool ok = nfused >= 0;
                 for (const BatchGroup& g : bp.groups) ok = ok && emulate_group(g, bp.table.data());
                 for (int i = 0; i < k; ++i) {
                     uint8_t* db = (uint8_t*)jobs[(size_t)i].dst;
@@ -619,8 +652,8 @@ int main(int argc, char** argv) {
                 std::string variants;
                 for (const BatchGroup& g : bp.groups)
                     variants += (variants.empty() ? "" : ",") + std::to_string(g.kind) + ":" + std::to_string(g.variant);
-                std::printf(ok ? "ok groups=%zu jobs=%u bytes=%llu variants=%s\n" : "err -1 no kernel\n",
-                            bp.groups.size(), bp.njobs, (unsigned long long)bp.bytes, variants.c_str());
+                std::printf(ok ? "ok groups=%zu jobs=%u bytes=%llu variants=%s fused=%d\n" : "err -1 no kernel\n",
+                            bp.groups.size(), bp.njobs, (unsigned long long)bp.bytes, variants.c_str(), nfused);
             }
             for (uint8_t* q : bufs) delete[] q;
         } else {

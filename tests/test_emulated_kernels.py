@@ -597,6 +597,24 @@ def test_emu_batched_uneven_jobs(seed, opts):
             (j["dims"], j["perm"], j["esize"])
 
 
+@pytest.mark.parametrize("max_g,outside", [(0, False), (2, True)])
+def test_emu_fused_launch_covers_each_workgroup_once(max_g, outside):
+    """One launch over a batch's groups: its workgroups map one to one onto the
+    groups' own (checked by the emulator for every workgroup).  Built-in plans fuse
+    whole; under a micro-tile cap of 2 the groups of G = 2 tiles stay outside."""
+    jobs = _batched_jobs(31, 80, 3000)
+    jobs += [_perm_job((48, 34, 8), (1, 0, 2), 8, 31900), _perm_job((50, 8), (1, 0), 2, 31901),
+             _perm_job((1,), (0,), 1, 31902), _perm_job((64, 64), (1, 0), 1, 31903),
+             _perm_job((62, 66), (1, 0), 4, 31904), _perm_job((64, 96), (1, 0), 2, 31905)]
+    status, outs = emu_runner.run([dict(op="batched", jobs=jobs, max_g=max_g)])[0]
+    assert status.startswith("ok"), status
+    groups, fused = (int(status.split(k + "=")[1].split()[0]) for k in ("groups", "fused"))
+    assert fused >= 2 and (fused < groups) == outside, status
+    for j, out in zip(jobs, outs):
+        assert np.array_equal(out, oracle.permute(j["input"], j["dims"], j["perm"], j["esize"])), \
+            (j["dims"], j["perm"], j["esize"])
+
+
 @pytest.mark.parametrize("chunk", [1, 3])
 def test_emu_chunked_entries(chunk):
     """Jobs cut into ranges of their own workgroups, ranges of different jobs

@@ -291,3 +291,39 @@ def test_small_jobs_take_the_batch_shape(rr):
     b.launch(torch.cuda.current_stream())
     torch.cuda.synchronize()
     _check_all_vs_oracle(J)
+
+
+@pytest.mark.parametrize("max_g", [0, 2])
+def test_fused_launch_matches_the_groups_one_by_one(rr, max_g):
+    """A small batch goes out as one launch over its groups (with max_g = 2 the G = 2
+    tiles keep launches of their own): the handle, a one-shot call and a captured
+    graph of the handle's launch each give the bytes that a launch per group gives."""
+    specs = _uneven(51, 200, 12000)
+    specs += [{"dims": d, "perm": p, "esize": e} for d, p, e in
+              (((64, 64), (1, 0), 1), ((96, 64), (1, 0), 2), ((62, 66), (1, 0), 4), ((40, 30, 24), (1, 0, 2), 4),
+               ((33, 77, 66), (1, 0, 2), 1), ((1000,), (0,), 3), ((0, 5), (1, 0), 4))]
+    J = Jobs(rr, specs, 51)
+    st = torch.cuda.current_stream()
+    rr.set_tile_override(max_g=max_g)
+    try:
+        _say("fused batch, max_g", max_g)
+        serial, fused = rr.Batch(J.arr, 8), rr.Batch(J.arr, 1)
+        serial.launch(st)
+        torch.cuda.synchronize()
+        _check_all_vs_oracle(J)
+        want = J.outs_device()
+        graph = torch.cuda.CUDAGraph()
+        plain = rr.Batch(J.arr, 0)
+        with torch.cuda.graph(graph):
+            plain.launch()
+        for rep in range(3):
+            for run in (lambda: fused.launch(st), lambda: graph.replay(),
+                        lambda: rr.check(rr.permute_batched_raw(J.arr, len(specs), st.cuda_stream))):
+                J.dst.zero_()
+                run()
+                torch.cuda.synchronize()
+                assert torch.equal(J.dst, want), rep
+        for b in (serial, fused, plain):
+            b.close()
+    finally:
+        rr.set_tile_override(0, 0, None)
