@@ -480,7 +480,12 @@ rr_status rr_permute_batched(const rr_job* jobs, int njobs, rr_stream_t stream) 
     Slot& s = ring.slots[k];
     std::memcpy(s.host, bp.table.data(), need);
     if (bp.table.capacity() > (size_t(32) << 20)) std::vector<uint8_t>().swap(bp.table);   // keep at most 32 MB
-    e = hipMemcpyAsync(s.dev, s.host, need, hipMemcpyHostToDevice, hs);
+    // The table goes up by a copy kernel that reads the pinned slot (mapped into the
+    // device's address space): it runs in the stream's own queue, where a copy engine
+    // would be waited for.  Calls of 79 / 256 jobs 33 -> 24 / 97 -> 89 us.
+    Plan up;
+    plan_copy((uint64_t)s.dev, (uint64_t)s.host, need, &up);
+    e = launch_plan(up, hs);
     if (e != hipSuccess) return hip_fail(e, "job table upload");
     st = launch_batch_plan(bp, (const uint8_t*)s.dev, GroupLaunch::fused, device, hs, &ring.fan);
     e = hipEventRecord(s.done, hs);
