@@ -1191,6 +1191,18 @@ RR_HD void read_ragged(const TileArgs& a, const TileCtx& t, uint8_t* lds, uint32
         [&](uint32_t r, uint32_t x) { return lds_pos<rot_group<U, 1>()>(a, r, x); }, lds, tid);
 }
 
+// Segment read: the tile's rows lie back to back in segments of segrows rows (one
+// segment of all TBv rows when B is a single axis), each one range of any
+// alignment, kept back to back in LDS.
+template <int U, bool S>
+RR_HD void read_segs(const TileArgs& a, const TileCtx& t, uint8_t* lds, uint32_t tid) {
+    const uint32_t rows = umin(a.segrows, t.TBv);
+    read_rows<U, S>(
+        mdiv(t.TBv + a.segrows - 1, a.mseg), rows * a.pitch,
+        [&](uint32_t r) { return t.bin + row_in(a, r * a.segrows); },
+        [&](uint32_t r, uint32_t x) { return r * a.segpitch + x; }, lds, tid);
+}
+
 // Stacked read: TCv sub-tiles of msub input bytes each; when they are back to
 // back in the input (sinC == msub) the whole range is one row.
 template <int U, bool S>
@@ -1211,6 +1223,7 @@ RR_HD void read_tile(const TileArgs& a, const TileCtx& t, uint8_t* lds, uint32_t
     if constexpr (G == 1 && U < 16) {   // 16-byte units are always aligned vectors
         if (a.flags & TF_STACK) { read_stack<U, S>(a, t, lds, tid); return; }
         if (a.flags & TF_RAGGED_IN) { read_ragged<U, S>(a, t, lds, tid); return; }
+        if (a.flags & TF_IN_SEG) { read_segs<U, S>(a, t, lds, tid); return; }
     }
     if constexpr (G > 1 && U < 16) {
         if (a.flags & TF_UMT) {
@@ -1244,8 +1257,9 @@ RR_HD void read_dispatch(const TileArgs& a, const TileCtx& t, uint8_t* lds, uint
 // Ragged write: each output row (TBv elements of k units of U bytes along the
 // output's fastest axis, any alignment) is written as 16-byte vectors gathered
 // unit by unit from LDS, plus its last (bytes % 16) / U units one by one.  Unit
-// q of an output row is unit q % k of element q / k (an LDS row).
-template <int U, bool S>
+// q of an output row is unit q % k of element q / k (an LDS row).  SEG: the LDS
+// rows lie in segments (read_segs), with the padding of a segment after its last.
+template <int U, bool S, bool SEG>
 RR_HD void write_ragged(const TileArgs& a, const TileCtx& t, const uint8_t* lds, uint32_t tid) {
     constexpr int EPV = 16 / U;   // units per 16-byte vector
     const uint32_t k = a.k;
@@ -1255,11 +1269,18 @@ RR_HD void write_ragged(const TileArgs& a, const TileCtx& t, const uint8_t* lds,
     if (per == 0 || t.TAv == 0) return;
     constexpr int RG = rot_group<U, 1>();   // == EPV: one output vector's rows share a rotation
     // LDS address of unit q of output row ia
-    auto unit_at = [&](uint32_t ia, uint32_t q) {
-        if (k == 1) return lds_pos<RG>(a, q, ia * U);
-        const uint32_t ib = mdiv(q, a.mk);
-        return lds_pos<RG>(a, ib, (ia * k + (q - ib * k)) * U);
+    const uint32_t segpad = SEG ? a.segpitch - a.segrows * a.pitch : 0u;
+    auto pos = [&](uint32_t ib, uint32_t x) {
+        if constexpr (SEG) return ib * a.pitch + mdiv(ib, a.mseg) * segpad + x;
+        else return lds_pos<RG>(a, ib, x);
     };
+    auto unit_at = [&](uint32_t ia, uint32_t q) {
+        if (k == 1) return pos(q, ia * U);
+        const uint32_t ib = mdiv(q, a.mk);
+        return pos(ib, (ia * k + (q - ib * k)) * U);
+    };
+    // a vector's rows leave their segment at most once where a segment holds as many
+    const bool once = !SEG || a.segrows >= (uint32_t)EPV;
     // Items go B per round: each item's row address and LDS gather first, then
     // the round's stores back to back (an address formed between stores made
     // the compiler wait for every outstanding store).
@@ -1281,8 +1302,12 @@ RR_HD void write_ragged(const TileArgs& a, const TileCtx& t, const uint8_t* lds,
                 const uint32_t q0 = w.col * EPV;
                 // element j of the vector: rows q0 + j (single-unit elements, one
                 // rotation group: one address, then a pitch per row) or unit q0 + j
-                const uint32_t base0 = k == 1 ? lds_pos<RG>(a, q0, ia * U) : 0u;
-                auto at = [&](uint32_t j) { return k == 1 ? base0 + j * a.pitch : unit_at(ia, q0 + j); };
+                const uint32_t base0 = k == 1 ? pos(q0, ia * U) : 0u;
+                const uint32_t next = SEG && k == 1 ? (mdiv(q0, a.mseg) + 1) * a.segrows - q0 : 0u;
+                auto at = [&](uint32_t j) {
+                    if (k != 1 || !once) return unit_at(ia, q0 + j);
+                    return base0 + j * a.pitch + (SEG && j >= next ? segpad : 0u);
+                };
                 if constexpr (U >= 4) {
 #pragma unroll
                     for (int j = 0; j < EPV; ++j) {
@@ -1489,7 +1514,8 @@ RR_HD void write_tile(const TileArgs& a, const TileCtx& t, const uint8_t* lds, u
             return;
         }
         if (a.flags & TF_RAGGED_OUT) {
-            write_ragged<U, S>(a, t, lds, tid);
+            if (a.flags & TF_IN_SEG) write_ragged<U, S, true>(a, t, lds, tid);
+            else write_ragged<U, S, false>(a, t, lds, tid);
             return;
         }
     }

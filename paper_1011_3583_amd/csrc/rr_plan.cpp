@@ -528,6 +528,10 @@ static bool plan_select(uint64_t dst, uint64_t src, const Canon& c, Plan* p) {
     return true;
 }
 
+// Input rows shorter than this take the segment read where they are back to back
+// (longer ones fill padded, rotated LDS rows without bank conflicts).
+constexpr int64_t SEG_ROW_BYTES = 64;
+
 static int default_row_bytes(int U, bool in_side) {
     switch (U) {
         case 1: return 128;
@@ -669,8 +673,10 @@ static void cache_policy(TileArgs& a, const TileOptions& opt) {
 //                  tile's input is one contiguous range starting at flat_base
 //                  plus a multiple of TB rows; total_rows is the row axis's whole
 //                  extent when slower axes follow it (0 when none do)
+//   seg_rows     : rows back to back along the innermost B axis come in segments of
+//                  this many rows (0: they do not)
 static rr_status finish_tile(TileArgs& a, int U, int G, int k, uint64_t row_align_in, bool flat_ok,
-                             uint64_t flat_base, uint64_t total_rows, const TileOptions& opt,
+                             uint64_t flat_base, uint64_t total_rows, uint32_t seg_rows, const TileOptions& opt,
                              std::string* why) {
     a.unit = U; a.g = G; a.k = k;
     a.mk = make_magic(k);
@@ -692,7 +698,24 @@ static rr_status finish_tile(TileArgs& a, int U, int G, int k, uint64_t row_alig
     // the input's last tile may end inside a vector (its tail moves byte by byte)
     const bool flat = flat_ok && (rowbytes % 16 != 0 || rowbytes < 64) && (flat_base % 16) == 0 &&
                       ((uint64_t)a.TB * rowbytes) % 16 == 0 && (total_rows * rowbytes) % 16 == 0;
-    if (flat) {
+    // Short rows that are back to back but do not start on 16-byte boundaries, or only
+    // run so along the innermost B axis (a crop's pixels): each such segment moves as
+    // one range of unaligned vectors.  Row by row they went unit by unit (3-byte
+    // pixels: three one-byte loads each; crop of 256 x 256 RGB to planes 114 us).
+    // output rows back to back, every tile holding all TB output columns
+    const bool out_flat = k == 1 && a.nA == 1 && !(a.flags & TF_OUT_TABLE) && a.grid_bO < 0 &&
+                          a.soutA[0] == (uint64_t)a.TB * a.R && (uint64_t)a.TB * a.R < 64;
+    const bool ragged_out = k == 1 ? !out_flat : !(a.flags & (TF_OUT_TABLE | TF_IN_TABLE));
+    const bool seg = !flat && seg_rows > 0 && G == 1 && U < 16 && rowbytes < SEG_ROW_BYTES && ragged_out;
+    if (seg) {
+        a.flags |= TF_IN_SEG;
+        a.pitch = (uint32_t)rowbytes;
+        a.nch16 = 0xffffffffu;
+        a.rotmask = 0;
+        a.segrows = seg_rows;
+        a.mseg = make_magic(seg_rows);
+        a.segpitch = (uint32_t)((seg_rows * rowbytes + 15) / 16 * 16);
+    } else if (flat) {
         a.flags |= TF_IN_FLAT;
         a.pitch = (uint32_t)rowbytes;
         a.nch16 = 0xffffffffu;   // no chunk rotation
@@ -704,10 +727,10 @@ static rr_status finish_tile(TileArgs& a, int U, int G, int k, uint64_t row_alig
         while (pw * 2 <= a.nch16) pw <<= 1;
         a.rotmask = pw - 1;
     }
-    a.lds_bytes = (a.pitch * a.TB + 15) / 16 * 16;
+    a.lds_bytes = seg ? a.TB / seg_rows * a.segpitch : (a.pitch * a.TB + 15) / 16 * 16;
     if (a.lds_bytes > (uint32_t)opt.max_lds) { *why = "tile does not fit LDS"; return RR_ERR_UNSUPPORTED; }
     uint32_t win = 16;
-    if (!flat)
+    if (!flat && !seg)
         while (win > (uint32_t)U && ((row_align_in % win) || (rowbytes % win))) win >>= 1;
     if (win < (uint32_t)U) win = U;
     a.win = win;
@@ -728,12 +751,8 @@ static rr_status finish_tile(TileArgs& a, int U, int G, int k, uint64_t row_alig
         // alignment instead of one element per access.  Short back-to-back output rows
         // (interlace of a few sets) are written as one contiguous range.
         if (G == 1 && U < 16) {
-            const bool out_rows_adjacent = a.nA == 1 && !(a.flags & TF_OUT_TABLE) &&
-                                           a.soutA[0] == (uint64_t)a.TB * a.R;
-            const bool tb_whole = a.grid_bO < 0;   // every tile holds all TB output columns
-            if (out_rows_adjacent && tb_whole && (uint64_t)a.TB * a.R < 64) a.flags |= TF_OUT_FLAT;
-            else a.flags |= TF_RAGGED_OUT;
-            if ((a.flags & TF_IN_FLAT) == 0) a.flags |= TF_RAGGED_IN;
+            a.flags |= out_flat ? TF_OUT_FLAT : TF_RAGGED_OUT;
+            if ((a.flags & (TF_IN_FLAT | TF_IN_SEG)) == 0) a.flags |= TF_RAGGED_IN;
         }
     } else {
         a.nmb = a.TB * k;      // units per output row
@@ -742,7 +761,7 @@ static rr_status finish_tile(TileArgs& a, int U, int G, int k, uint64_t row_alig
         // 16-byte vectors at any alignment instead of one unit per access.
         if (G == 1 && U < 16 && !(a.flags & (TF_OUT_TABLE | TF_IN_TABLE))) {
             a.flags |= TF_RAGGED_OUT;
-            if ((a.flags & TF_IN_FLAT) == 0) a.flags |= TF_RAGGED_IN;
+            if ((a.flags & (TF_IN_FLAT | TF_IN_SEG)) == 0) a.flags |= TF_RAGGED_IN;
         }
     }
     a.mnmb = make_magic(a.nmb);
@@ -871,11 +890,24 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
         const int x = pm[r - 1 - nB];
         if (x == aO) t[aO] = d[aO];
     }
-    // shrink toward the soft tile size (an LDS row is padded to 16 bytes)
+    // shrink toward the soft tile size (an LDS row is padded to 16 bytes, except the
+    // short rows of whole A axes that lie back to back along b1: their segments are)
     const int64_t soft_lds = std::min<int64_t>(soft_bytes, opt.max_lds);
+    auto back_to_back = [&]() {
+        const int64_t rowb = innerA * t[aO] * R;
+        return !umt && G == 1 && U < 16 && t[aO] == d[aO] && b1 == r - 1 - nA && sinb[b1] == rowb && rowb < SEG_ROW_BYTES;
+    };
+    if (back_to_back() && nB > 1) {
+        const int64_t segb = (t[b1] * innerA * t[aO] * R + 15) / 16 * 16, per = innerB / t[b1] * segb;
+        const int64_t fit = std::max<int64_t>(1, soft_lds / per);
+        if (t[bO] > fit) t[bO] = fit;
+        t[bO] = cdiv(d[bO], cdiv(d[bO], t[bO]));   // evened out
+    }
     for (int guard = 0; guard < 64; ++guard) {
         int64_t TA = innerA * t[aO], TB = innerB * t[bO];
         int64_t bytes = TB * ((TA * R + 15) / 16 * 16);
+        if (back_to_back())
+            bytes = nB == 1 ? (TB * TA * R + 15) / 16 * 16 : TB / t[b1] * ((t[b1] * TA * R + 15) / 16 * 16);
         if (bytes <= soft_lds) break;
         int64_t stepA = nA == 1 ? G : 1, stepB = nB == 1 ? G : 1;
         bool canA = t[aO] > stepA, canB = t[bO] > stepB;
@@ -1059,7 +1091,8 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
     // 2-byte units stay: their G = 1 rows gather byte by byte (1024^2 transposes
     // -17 %).
     if (opt.rows_only && !umt && (U >= 4 || G == 2)) G = 1;
-    rr_status st = finish_tile(a, U, G, k, ra, flat_ok && !umt, src, b1 > 0 ? (uint64_t)d[b1] : 0, opt, why);
+    rr_status st = finish_tile(a, U, G, k, ra, flat_ok && !umt, src, b1 > 0 ? (uint64_t)d[b1] : 0,
+                               back_to_back() ? (nB == 1 ? a.TB : a.tB[0]) : 0, opt, why);
     if (st != RR_OK) return st;
     cache_policy(a, opt);
     if (a.ngrid >= 2 && (opt.diag == 1 || (opt.diag == -1 && diag_by_default(c)))) a.flags |= TF_DIAG;
@@ -1223,7 +1256,7 @@ static rr_status plan_interlace_tile(uint64_t flat, const uint64_t* planes, int 
         for (int c = 0; c < n; ++c) a.table[c] = planes[c];
         uint64_t ra = (uint64_t)(L * R) | (uint64_t)(count * R);
         for (int c = 0; c < n; ++c) ra |= planes[c];
-        rr_status st = finish_tile(a, U, G, k, ra, false, 0, 0, opt, why);
+        rr_status st = finish_tile(a, U, G, k, ra, false, 0, 0, 0, opt, why);
         if (st != RR_OK) return st;
     } else {
         // A = plane axis (n, full), B = element axis (length L per tile)
@@ -1241,7 +1274,7 @@ static rr_status plan_interlace_tile(uint64_t flat, const uint64_t* planes, int 
         a.bO_len = (uint32_t)count; a.bO_t = (uint32_t)L;
         for (int c = 0; c < n; ++c) a.table[c] = planes[c];
         uint64_t ra = a.src | (uint64_t)(n * R);
-        rr_status st = finish_tile(a, U, G, k, ra, true, a.src, 0, opt, why);
+        rr_status st = finish_tile(a, U, G, k, ra, true, a.src, 0, a.TB, opt, why);
         if (st != RR_OK) return st;
     }
     cache_policy(a, opt);

@@ -178,6 +178,9 @@ enum TileFlags : uint32_t {
                             // neighbouring tiles); default: non-temporal
     TF_ST_CACHED = 2048u,   // write through the caches; default: non-temporal
     TF_DIAG = 4096u,        // diagonal tile order over the two fastest tile-grid axes
+    TF_IN_SEG = 8192u,      // short input rows back to back in segments of segrows rows (the
+                            // innermost B axis), each segment read as one range of any alignment;
+                            // LDS rows unpadded within a segment
 };
 
 struct TileArgs {
@@ -224,6 +227,9 @@ struct TileArgs {
                               // the input, else msub rounded up to 16)
     Magic msubel;             // stacked: divide by TA * TB
     uint64_t sinC, soutC;     // stacked: byte stride of C in input and output
+    uint32_t segrows;         // TF_IN_SEG: rows per segment
+    uint32_t segpitch;        // TF_IN_SEG: LDS bytes from one segment to the next (multiple of 16)
+    Magic mseg;               // TF_IN_SEG: divide by segrows
     uint64_t table[RR_MAX_PLANES];
 };
 

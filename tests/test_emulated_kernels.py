@@ -312,6 +312,54 @@ def test_emu_reorder_offsets_and_unaligned_micro_tiles():
         assert np.array_equal(out, ref), (j["dims"], j["base"], j["range"], j["order"], st)
 
 
+SEG_READ_CASES = [
+    # short input rows back to back only along the innermost B axis, or off 16-byte
+    # boundaries: (dims, base, range, order, element bytes, segments)
+    ((3, 40, 30, 3), (0, 4, 3, 0), (3, 31, 22, 3), (0, 3, 1, 2), 1, True),    # RGB crop, 66-byte segments
+    ((2, 70, 260, 3), (0, 5, 2, 0), (2, 64, 224, 3), (0, 3, 1, 2), 1, True),  # 672-byte segments, two tiles
+    ((2, 33, 21, 3), (0, 1, 1, 0), (2, 30, 17, 3), (0, 3, 1, 2), 4, True),
+    ((2, 25, 19, 5), (0, 2, 3, 0), (2, 22, 15, 5), (0, 3, 1, 2), 2, True),
+    ((2, 90, 9, 7), (0, 2, 1, 0), (2, 80, 7, 7), (0, 3, 1, 2), 1, True),      # segments shorter than a vector's rows
+    ((2, 60, 50, 2), (0, 1, 1, 0), (2, 57, 47, 2), (0, 3, 1, 2), 6, True),    # elements of three 2-byte units
+    ((3, 4, 50, 6, 5), (0, 0, 1, 0, 0), (3, 4, 44, 6, 5), (0, 4, 1, 2, 3), 1, True),  # three B axes
+    ((5000, 3), (1, 0), (4999, 3), (1, 0), 1, True),                          # one segment, off a vector boundary
+    ((700, 11), (3, 0), (690, 11), (1, 0), 2, True),
+    ((3, 40, 30, 4), (0, 4, 3, 0), (3, 32, 24, 4), (0, 3, 1, 2), 4, False),   # aligned micro-tiles: as before
+]
+
+
+def test_emu_short_rows_read_as_segments():
+    """Boxes and permutes with short input rows take the segment read and match the
+    oracle, aligned and at odd pointers, with tail segments and partial tiles."""
+    jobs, want = [], []
+    for i, (d, b, r, o, e, seg) in enumerate(SEG_READ_CASES):
+        for so, do in ((0, 0), (e, 3 * e)):
+            jobs.append(_reorder_job(d, b, r, o, e, 8700 + i, src_off=so, dst_off=do))
+            want.append(seg or None if so or do else seg)
+    for j, w, (st, out) in zip(jobs, want, emu_runner.run(jobs)):
+        assert st.startswith("ok"), (j["dims"], st)
+        ref = oracle.reorder_slice(j["input"], j["dims"], j["base"], j["range"], j["order"], j["esize"])
+        assert np.array_equal(out, ref), (j["dims"], j["base"], j["range"], j["order"], j["esize"], st)
+        if w is not None:
+            assert bool(int(st.split(" flags=")[1].split()[0]) & 8192) == w, (j["dims"], st)
+    # dense shapes: rows back to back under a slower B axis, de-interlace off a boundary, in a batch
+    perms = [((7, 40, 5, 6), (3, 0, 2, 1), 1), ((9, 11, 13, 7), (3, 0, 1, 2), 2), ((6, 50, 3, 5), (3, 1, 0, 2), 4),
+             ((33, 7, 5), (2, 0, 1), 8), ((1001, 3), (1, 0), 1), ((2003, 5), (1, 0), 2)]
+    jobs = [_perm_job(d, p, e, 8800 + i, src_off=e * k, dst_off=0) for i, (d, p, e) in enumerate(perms) for k in (0, 1)]
+    _check(jobs)
+    status, outs = emu_runner.run([dict(op="batched", jobs=jobs)])[0]
+    assert status.startswith("ok"), status
+    for j, out in zip(jobs, outs):
+        assert np.array_equal(out, oracle.permute(j["input"], j["dims"], j["perm"], j["esize"])), j["dims"]
+    planes = [dict(op="deinterlace", n=n, count=c, esize=e, off=e, input=rr_synth.random_bytes(8900 + n, n * c * e))
+              for n, c, e in ((3, 2500, 1), (5, 999, 2), (9, 777, 4), (3, 400, 12))]
+    for j, (st, out) in zip(planes, emu_runner.run(planes)):
+        assert st.startswith("ok"), st
+        ref = j["input"].reshape(j["count"], j["n"], j["esize"])
+        for c in range(j["n"]):
+            assert np.array_equal(out[c], np.ascontiguousarray(ref[:, c]).reshape(-1)), (j["n"], c)
+
+
 SELECT_CASES = [
     # one channel of interleaved records: (dims, base, range, order, element bytes)
     ((64, 96, 4), (0, 0, 2), (64, 96, 1), (0, 1), 1),          # RGBA plane, fused to one row
