@@ -453,7 +453,8 @@ rr_status rr_interlace_describe(const void* flat, const void* const* planes, int
  * 16-byte boundary and every set a whole number of 16-byte vectors, are joined or
  * split in registers, one 16-byte vector of each set per thread; the cache bits
  * then say whether the joined side goes through the caches, streamed by
- * default).  RR_TILE_DIAG / RR_TILE_NO_DIAG switch the diagonal tile order on or
+ * default; so are sets of at least 256 KiB at any alignment and length, both
+ * sides streamed).  RR_TILE_DIAG / RR_TILE_NO_DIAG switch the diagonal tile order on or
  * off everywhere; with neither the planner uses it for 2-D transposes of 1-8-byte
  * elements whose rows are a power of two of at least 4 KiB on both sides
  * (RR_ERR_INVALID_ARG for both flags). */

@@ -183,12 +183,29 @@ RR_HD void gstore16u(uint8_t* p, const uint32_t (&w)[4]) {
 #endif
 }
 
-// W bytes (2, 4, 8, 16) at any byte alignment.
+// W bytes (1, 2, 4, 8; stores also 16) at any byte alignment.
 #if defined(__HIP_DEVICE_COMPILE__)
 typedef uint32_t rr_u32x2_u __attribute__((ext_vector_type(2), aligned(1)));
 typedef uint32_t rr_u32_u __attribute__((aligned(1)));
 typedef uint16_t rr_u16_u __attribute__((aligned(1)));
 #endif
+template <int W>
+RR_HD void gload_u(const uint8_t* p, uint32_t (&w)[NWords<W>::value]) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (W == 8) {
+        const rr_u32x2_u v = *as_global<rr_u32x2_u>(p);
+        w[0] = v.x; w[1] = v.y;
+    } else if constexpr (W == 4) {
+        w[0] = *as_global<rr_u32_u>(p);
+    } else if constexpr (W == 2) {
+        w[0] = *as_global<rr_u16_u>(p);
+    } else {
+        vload_t<W, false, true>(p, w);
+    }
+#else
+    vload_t<W, false, true>(p, w);
+#endif
+}
 template <int W, bool S = true>
 RR_HD void gstore_u(uint8_t* p, const uint32_t (&w)[NWords<W>::value]) {
     if constexpr (W == 16) {
@@ -671,13 +688,25 @@ RR_HD void sched_fence() {
 // [b * R * NT, (b + 1) * R * NT), chunk r of its wave w starting at
 // (b * R + r) * NT + w * 64.  The joined side goes through the caches when C is
 // true, else is streamed like the set side.  Only chunks that hold the last
-// group check vector bounds.  `off` is added to every set and joined pointer
+// group check vector bounds.  Vectors lie on 16-byte boundaries, or
+// with ANY at any alignment.  `off` is added to every set and joined pointer
 // (the batch's byte offset).  lds: R * NT * N * 16 bytes.
 RR_HD uint64_t weave_chunk(uint32_t block, int r, uint32_t wave, int R) {
     return ((uint64_t)block * R + r) * NT + wave * 64u;
 }
 
-template <int U, int N, bool DE, bool C, int R>
+template <bool ANY, bool S>
+RR_HD void weave_load(const uint8_t* p, uint32_t (&w)[4]) {
+    if constexpr (ANY) gload16u<S>(p, w);
+    else gload<16, S>(p, w);
+}
+template <bool ANY, bool S>
+RR_HD void weave_store(uint8_t* p, const uint32_t (&w)[4]) {
+    if constexpr (ANY) gstore16u<S>(p, w);
+    else gstore<16, S>(p, w);
+}
+
+template <int U, int N, bool DE, bool C, int R, bool ANY = false>
 RR_HD void weave_stage(const WeaveArgs& a, uint32_t block, uint64_t off, uint8_t* lds, uint32_t tid) {
     constexpr uint32_t WV = 64, NW = NT / WV;
     const uint32_t wave = tid / WV, lane = tid % WV;
@@ -691,7 +720,7 @@ RR_HD void weave_stage(const WeaveArgs& a, uint32_t block, uint64_t off, uint8_t
             if (ok[r])
 #pragma unroll
                 for (int s = 0; s < N; ++s)
-                    gload<16>(reinterpret_cast<const uint8_t*>(a.planes[s]) + off + v * 16u, in[r][s]);
+                    weave_load<ANY, true>(reinterpret_cast<const uint8_t*>(a.planes[s]) + off + v * 16u, in[r][s]);
         }
         sched_fence();
 #pragma unroll
@@ -712,7 +741,7 @@ RR_HD void weave_stage(const WeaveArgs& a, uint32_t block, uint64_t off, uint8_t
             for (int r = 0; r < R; ++r)
 #pragma unroll
                 for (int k = 0; k < N; ++k)
-                    gload<16, !C>(joined + (weave_chunk(block, r, wave, R) * N + k * WV + lane) * 16u, x[r][k]);
+                    weave_load<ANY, !C>(joined + (weave_chunk(block, r, wave, R) * N + k * WV + lane) * 16u, x[r][k]);
             sched_fence();
 #pragma unroll
             for (int r = 0; r < R; ++r)
@@ -729,7 +758,7 @@ RR_HD void weave_stage(const WeaveArgs& a, uint32_t block, uint64_t off, uint8_t
                     const uint64_t j = weave_chunk(block, r, wave, R) * N + m;
                     if (j < total) {
                         uint32_t x[4];
-                        gload<16, !C>(joined + j * 16u, x);
+                        weave_load<ANY, !C>(joined + j * 16u, x);
                         sstore<16>(lds + (uint64_t)(r * NW + wave) * WV * N * 16u + 16u * weave_slot<N>(m), x);
                     }
                 }
@@ -737,7 +766,7 @@ RR_HD void weave_stage(const WeaveArgs& a, uint32_t block, uint64_t off, uint8_t
     }
 }
 
-template <int U, int N, bool DE, bool C, int R>
+template <int U, int N, bool DE, bool C, int R, bool ANY = false>
 RR_HD void weave_finish(const WeaveArgs& a, uint32_t block, uint64_t off, const uint8_t* lds, uint32_t tid) {
     constexpr uint32_t WV = 64, NW = NT / WV;
     const uint32_t wave = tid / WV, lane = tid % WV;
@@ -756,7 +785,7 @@ RR_HD void weave_finish(const WeaveArgs& a, uint32_t block, uint64_t off, const 
             for (int r = 0; r < R; ++r)
 #pragma unroll
                 for (int k = 0; k < N; ++k)
-                    gstore<16, !C>(joined + (weave_chunk(block, r, wave, R) * N + k * WV + lane) * 16u, x[r][k]);
+                    weave_store<ANY, !C>(joined + (weave_chunk(block, r, wave, R) * N + k * WV + lane) * 16u, x[r][k]);
         } else {
 #pragma unroll
             for (int r = 0; r < R; ++r)
@@ -767,7 +796,7 @@ RR_HD void weave_finish(const WeaveArgs& a, uint32_t block, uint64_t off, const 
                     if (j < total) {
                         uint32_t x[4];
                         sload<16>(lds + (uint64_t)(r * NW + wave) * WV * N * 16u + 16u * weave_slot<N>(m), x);
-                        gstore<16, !C>(joined + j * 16u, x);
+                        weave_store<ANY, !C>(joined + j * 16u, x);
                     }
                 }
         }
@@ -782,9 +811,22 @@ RR_HD void weave_finish(const WeaveArgs& a, uint32_t block, uint64_t off, const 
             for (int k = 0; k < N; ++k) sload<16>(w + 16u * weave_slot<N>(lane * N + k), in[k]);
             weave_regs<U, N, true>(in, out);
 #pragma unroll
-            for (int s = 0; s < N; ++s) gstore<16>(reinterpret_cast<uint8_t*>(a.planes[s]) + off + v * 16u, out[s]);
+            for (int s = 0; s < N; ++s) weave_store<ANY, true>(reinterpret_cast<uint8_t*>(a.planes[s]) + off + v * 16u, out[s]);
         }
     }
+}
+
+// The elements of each set past its last whole vector, one per thread.
+template <int U, int N, bool DE>
+RR_HD void weave_tail(const WeaveArgs& a, uint64_t off, uint32_t tid) {
+    if (tid >= a.tail * N) return;
+    const uint32_t i = tid / N, c = tid - i * N;
+    const uint64_t first = (uint64_t)a.nvec * (16 / U) + i;
+    uint8_t* set = reinterpret_cast<uint8_t*>(a.planes[c]) + off + first * U;
+    uint8_t* joined = reinterpret_cast<uint8_t*>(a.joined) + off + (first * N + c) * U;
+    uint32_t e[NWords<U>::value];
+    gload_u<U>(DE ? joined : set, e);
+    gstore_u<U>(DE ? set : joined, e);
 }
 
 // ----------------------------------------------------------------- strided select

@@ -77,13 +77,13 @@ __global__ __launch_bounds__(NT) void k_select(const SelectArgs a) {
 // Lanes of one wave exchange vectors through their own LDS region: LDS
 // operations of a wave complete in issue order, so a wave-level barrier (which
 // keeps the compiler from moving the reads above the writes) is enough.
-template <int U, int N, bool DE, bool C, int R>
+template <int U, int N, bool DE, bool C, int R, bool ANY>
 __device__ __forceinline__ void weave_block(const WeaveArgs& a, uint32_t block, uint64_t off, uint8_t* lds) {
-    weave_stage<U, N, DE, C, R>(a, block, off, lds, threadIdx.x);
+    weave_stage<U, N, DE, C, R, ANY>(a, block, off, lds, threadIdx.x);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    weave_finish<U, N, DE, C, R>(a, block, off, lds, threadIdx.x);
+    weave_finish<U, N, DE, C, R, ANY>(a, block, off, lds, threadIdx.x);
 }
 
 // Workgroups [b * bpb, (b + 1) * bpb) cover batch b (one batch for rr_interlace).
@@ -93,8 +93,28 @@ __global__ __launch_bounds__(NT) void k_weave(const WeaveArgs a) {
     const uint32_t batch = blockIdx.x / a.bpb;
     const uint32_t block = blockIdx.x - batch * a.bpb;
     const uint64_t off = (uint64_t)batch * a.bstride;
-    if (a.cached) weave_block<U, N, DE, true, R>(a, block, off, lds);
-    else weave_block<U, N, DE, false, R>(a, block, off, lds);
+    if (a.cached) weave_block<U, N, DE, true, R, false>(a, block, off, lds);
+    else weave_block<U, N, DE, false, R, false>(a, block, off, lds);
+}
+
+// The same for sets off 16-byte boundaries or that end inside a vector: vectors at
+// any alignment, a wave's still 1 KiB of consecutive bytes, both sides streamed.
+// Bound by HBM as the aligned kernel is; the tile these went to before gathers its
+// output element by element.  300 MiB, interlace / de-interlace, tile -> here, GB/s:
+// 3 byte sets of odd length 3319 / 4746 -> 6252 / 6243, 8 of them 3699 / 1191 ->
+// 6100 / 5700, 3 float sets 5490 / 5825 -> 6250 / 6240; off a boundary 3412 / 591
+// (bytes) and 5412 / 3691 (floats) -> 5640 / 5590 and 5790 / 5790.  Cached stores
+// lost 2-7 % on sets off 128-byte lines.  A kernel of its own: a runtime choice
+// between streamed and cached stores of the same values is merged by the compiler
+// into cached ones.
+template <int U, int N, bool DE, int R>
+__global__ __launch_bounds__(NT) void k_weave_any(const WeaveArgs a) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[R * NT * N * 16];
+    const uint32_t batch = blockIdx.x / a.bpb;
+    const uint32_t block = blockIdx.x - batch * a.bpb;
+    const uint64_t off = (uint64_t)batch * a.bstride;
+    weave_block<U, N, DE, false, R, true>(a, block, off, lds);
+    if (a.tail && block == 0) weave_tail<U, N, DE>(a, off, threadIdx.x);
 }
 
 template <int U, int G>
@@ -189,19 +209,23 @@ static hipError_t launch_select(const SelectArgs& a, uint32_t grid, hipStream_t 
 }
 
 // Two chunks per wave are built for up to four sets only (the planner's choice).
+template <int U, int N, int R>
+static hipError_t launch_weave_unr(const WeaveArgs& a, uint32_t grid, hipStream_t st) {
+    if (!a.any) {
+        if (a.de) hipLaunchKernelGGL((k_weave<U, N, true, R>), dim3(grid), dim3(NT), 0, st, a);
+        else hipLaunchKernelGGL((k_weave<U, N, false, R>), dim3(grid), dim3(NT), 0, st, a);
+    } else {
+        if (a.de) hipLaunchKernelGGL((k_weave_any<U, N, true, R>), dim3(grid), dim3(NT), 0, st, a);
+        else hipLaunchKernelGGL((k_weave_any<U, N, false, R>), dim3(grid), dim3(NT), 0, st, a);
+    }
+    return hipGetLastError();
+}
+
 template <int U, int N>
 static hipError_t launch_weave_un(const WeaveArgs& a, uint32_t grid, hipStream_t st) {
-    if (a.chunks == 1) {
-        if (a.de) hipLaunchKernelGGL((k_weave<U, N, true, 1>), dim3(grid), dim3(NT), 0, st, a);
-        else hipLaunchKernelGGL((k_weave<U, N, false, 1>), dim3(grid), dim3(NT), 0, st, a);
-        return hipGetLastError();
-    }
+    if (a.chunks == 1) return launch_weave_unr<U, N, 1>(a, grid, st);
     if constexpr (N <= 4) {
-        if (a.chunks == 2) {
-            if (a.de) hipLaunchKernelGGL((k_weave<U, N, true, 2>), dim3(grid), dim3(NT), 0, st, a);
-            else hipLaunchKernelGGL((k_weave<U, N, false, 2>), dim3(grid), dim3(NT), 0, st, a);
-            return hipGetLastError();
-        }
+        if (a.chunks == 2) return launch_weave_unr<U, N, 2>(a, grid, st);
     }
     return hipErrorInvalidValue;
 }

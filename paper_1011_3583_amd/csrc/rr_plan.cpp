@@ -1101,8 +1101,11 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
     return RR_OK;
 }
 
-// 2-8 sets of 1-8-byte elements on 16-byte boundaries, a whole number of
-// 16-byte vectors each: joined and split in registers, vectors swapped between
+// Sets off 16-byte boundaries, or that end inside a vector, take the register
+// path from this size; smaller ones are bound by their launch on either path.
+constexpr int64_t WEAVE_UNALIGNED_SET_BYTES = 256 << 10;
+
+// 2-8 sets of 1-8-byte elements: joined and split in registers, vectors swapped between
 // lanes through a wave-private LDS region (no tile, no workgroup barrier).
 // nbatch problems lie bstride bytes apart on both sides.  False (nothing
 // planned) where these conditions do not hold.
@@ -1110,13 +1113,14 @@ static bool plan_weave(uint64_t flat, const uint64_t* planes, int n, int64_t cou
                        int64_t nbatch, uint64_t bstride, const TileOptions& opt, Plan* p) {
     const bool pow2_unit = esize == 1 || esize == 2 || esize == 4 || esize == 8;
     if (!opt.weave || !pow2_unit || n < 2 || n > WEAVE_MAX_SETS || count <= 0 || nbatch < 1) return false;
-    // eight-set de-interlaces, and interlaces of eight sets of 4-8-byte
-    // elements, stay on the tile (measured 4-10 % faster from cold caches)
-    if (n == 8 && (de || esize >= 4)) return false;
     bool aligned = flat % 16 == 0 && (count * esize) % 16 == 0 && bstride % 16 == 0;
     for (int c = 0; c < n; ++c) aligned = aligned && planes[c] % 16 == 0;
     const int64_t nvec = count * esize / 16;
-    if (!aligned || nvec > 0x7fffffffLL) return false;
+    if (nvec > 0x7fffffffLL) return false;
+    // eight-set de-interlaces, and interlaces of eight sets of 4-8-byte
+    // elements, stay on the tile (measured 4-10 % faster from cold caches)
+    if (aligned && n == 8 && (de || esize >= 4)) return false;
+    if (!aligned && count * esize < WEAVE_UNALIGNED_SET_BYTES) return false;
     // two chunks per wave (2 * n loads in flight per lane) up to three sets and
     // for a four-set de-interlace; one from four sets on (two would take 32 KiB
     // or more of LDS per workgroup, cutting the waves per CU to 20 or fewer)
@@ -1130,6 +1134,8 @@ static bool plan_weave(uint64_t flat, const uint64_t* planes, int n, int64_t cou
     w.joined = flat;
     w.bstride = nbatch > 1 ? bstride : 0;
     w.nvec = (uint32_t)nvec;
+    w.tail = (uint32_t)((count * esize - nvec * 16) / esize);
+    w.any = aligned ? 0u : 1u;
     w.n = (uint32_t)n;
     w.unit = (uint32_t)esize;
     w.de = de ? 1u : 0u;
@@ -1138,7 +1144,7 @@ static bool plan_weave(uint64_t flat, const uint64_t* planes, int n, int64_t cou
     // odd number of sets, which measured 0.5-7 % faster through the caches from
     // cold caches (even numbers of sets 0-5 % slower; cached joined loads of a
     // de-interlace 15-40 % slower)
-    w.cached = opt.cache >= 0 ? (uint32_t)((opt.cache >> (de ? 0 : 1)) & 1) : (!de && n % 2 == 1) ? 1u : 0u;
+    w.cached = !aligned ? 0u : opt.cache >= 0 ? (uint32_t)((opt.cache >> (de ? 0 : 1)) & 1) : (!de && n % 2 == 1) ? 1u : 0u;
     w.chunks = chunks;
     w.bpb = (uint32_t)bpb;
     p->grid = (uint32_t)(bpb * nbatch);

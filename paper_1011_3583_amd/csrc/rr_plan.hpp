@@ -138,10 +138,10 @@ struct SelectArgs {
 };
 
 // Interlace / de-interlace in registers: N planes of U-byte elements (N in
-// 2..WEAVE_MAX_SETS, U in 1, 2, 4, 8), every pointer 16-byte aligned and every
-// plane a whole number of 16-byte vectors.  Thread v joins (or splits) vector v
+// 2..WEAVE_MAX_SETS, U in 1, 2, 4, 8).  Thread v joins (or splits) vector v
 // of each plane and the N consecutive 16-byte vectors of the joined array that
-// hold the same elements.
+// hold the same elements; the `tail` elements of each plane past its last whole
+// vector move one by one.
 constexpr int WEAVE_MAX_SETS = 8;
 struct WeaveArgs {
     uint64_t planes[WEAVE_MAX_SETS];   // interlace: the sets read; de-interlace: the sets written
@@ -155,6 +155,8 @@ struct WeaveArgs {
     uint32_t cached;          // 1: the joined side goes through the caches, 0: streamed
     uint32_t chunks;          // chunks of 64 groups per wave (1 or 2)
     uint32_t bpb;             // workgroups per batch
+    uint32_t tail;            // elements per plane past its last whole vector
+    uint32_t any;             // 1: some vector lies off a 16-byte boundary, or tail > 0
     uint32_t pad_;
 };
 

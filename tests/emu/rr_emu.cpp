@@ -269,12 +269,14 @@ static void run_select_rm(const SelectArgs& a, uint32_t grid) {
 
 template <int U, int N, bool DE, int R>
 static void run_weave_undr(const WeaveArgs& a, uint32_t grid) {
+    if (!a.any && a.tail) std::abort();   // the aligned kernel moves no tail
     for (uint32_t g = 0; g < grid; ++g) {
         const uint32_t batch = g / a.bpb, b = g - batch * a.bpb;
         const uint64_t off = (uint64_t)batch * a.bstride;
         std::vector<uint8_t> lds((size_t)R * NT * N * 16, 0xA5);
         for (uint32_t tid = 0; tid < (uint32_t)NT; ++tid) weave_stage<U, N, DE, false, R>(a, b, off, lds.data(), tid);
         for (uint32_t tid = 0; tid < (uint32_t)NT; ++tid) weave_finish<U, N, DE, false, R>(a, b, off, lds.data(), tid);
+        for (uint32_t tid = 0; b == 0 && tid < (uint32_t)NT; ++tid) weave_tail<U, N, DE>(a, off, tid);
     }
 }
 

@@ -645,6 +645,33 @@ def test_emu_batched_uneven_jobs(seed, opts):
             (j["dims"], j["perm"], j["esize"])
 
 
+@pytest.mark.parametrize("e", [1, 2, 4, 8])
+def test_emu_register_interlace_off_vector_boundaries(e):
+    """Sets of at least 256 KiB off 16-byte boundaries, or ending inside a vector, take
+    the register path as well (from exactly that size; one element fewer keeps the
+    tile): interlace, de-interlace and the permutes of the same shape match the oracle."""
+    edge = (256 << 10) // e
+    jobs, want = [], []
+    for n, count, off in [(2, edge, e), (3, edge + 1, 0), (3, edge - 1, 0), (5, edge + 16 // e - 1, 3 * e), (8, edge + 5, 0)]:
+        off = 0 if e == 8 and off % 16 == 0 else off
+        planes = [rr_synth.random_bytes(13000 + 10 * n + c + e, count * e) for c in range(n)]
+        flat = rr_synth.random_bytes(13500 + n + e, n * count * e)
+        jobs += [dict(op="interlace", n=n, count=count, esize=e, off=off, planes=planes),
+                 dict(op="deinterlace", n=n, count=count, esize=e, off=off, input=flat)]
+        want += ["weave" if count >= edge else "tile"] * 2
+    for dims, perm in [((edge + 3, 3), (1, 0)), ((3, edge + 3), (1, 0)), ((2, edge + 1, 2), (0, 2, 1))]:
+        jobs.append(_perm_job(dims, perm, e, 13800 + dims[0] % 7, src_off=e, dst_off=0))
+        want.append("weave")
+    for j, k, (status, out) in zip(jobs, want, emu_runner.run(jobs)):
+        assert status.startswith("ok") and f"class={k}" in status, (j["op"], j.get("n"), j.get("count"), status)
+        if j["op"] == "permute":
+            assert np.array_equal(out, oracle.permute(j["input"], j["dims"], j["perm"], e)), j["dims"]
+        elif j["op"] == "interlace":
+            assert np.array_equal(out, oracle.interlace(j["planes"], e)), j["n"]
+        else:
+            assert all(np.array_equal(o, r) for o, r in zip(out, oracle.deinterlace(j["input"], j["n"], e))), j["n"]
+
+
 @pytest.mark.parametrize("max_g,outside", [(0, False), (2, True)])
 def test_emu_fused_launch_covers_each_workgroup_once(max_g, outside):
     """One launch over a batch's groups: its workgroups map one to one onto the

@@ -280,6 +280,32 @@ def test_register_interlace(rr, e):
         rr.set_tile_override()
 
 
+@pytest.mark.parametrize("e", [1, 2, 4, 8])
+def test_register_interlace_off_vector_boundaries(rr, e):
+    """Sets of 256 KiB and more at any alignment and length through the register path:
+    every number of sets, both directions, one and several waves past a whole number
+    of workgroups, and the permutes of the same shape, bit-exact."""
+    rr.set_tile_override()
+    for n in range(2, 9):
+        for count, off in [((256 << 10) // e, e), ((256 << 10) // e + 1, 0), ((300 << 10) // e + 16 // e - 1, 3)]:
+            if n > 2 and (n + count) % 2:   # half of the cases for the larger numbers of sets
+                count += 16 // e
+            _say("register interlace off boundaries", n, count, e, off)
+            base = (1 << 40) + off
+            fake = [base + (c + 1) * (count * e + 4096) * n for c in range(n)]
+            if off or count * e % 16:
+                assert rr.interlace_describe(base, fake, count, e)["class"] == "weave"
+            planes = [rr_synth.random_bytes(14000 + 100 * n + 10 * e + c, count * e) for c in range(n)]
+            assert np.array_equal(gpu_interlace(rr, planes, e, off), oracle.interlace(planes, e)), (n, e)
+            x = rr_synth.random_bytes(14500 + 100 * n + e, n * count * e)
+            got = gpu_deinterlace(rr, x, n, e, off)
+            assert all(np.array_equal(g, r) for g, r in zip(got, oracle.deinterlace(x, n, e))), (n, e)
+    big = (256 << 10) // e + 3
+    for i, (dims, perm) in enumerate([((big, 3), (1, 0)), ((5, big), (1, 0)), ((3, big, 2), (0, 2, 1))]):
+        check_permute(rr, dims, perm, e, 14900 + i, e, 0)
+        check_permute(rr, dims, perm, e, 14910 + i, 0, 5)
+
+
 def test_register_interlace_permutes(rr):
     """Small-axis transposes, batched or not, through the register interlace (and at
     a 4-byte offset through the tile), bit-exact."""
