@@ -430,8 +430,7 @@ rr_status rr_tune_permute(void* dst, const void* src, int ndim, const int64_t* d
         std::string why;
         if (plan_permute((uint64_t)dst, (uint64_t)src, c, o, &p, &why) != RR_OK) continue;
         // skip candidates that plan to a launch already timed
-        std::string sig = describe(p);
-        sig += " o" + std::to_string(cd.order < 0 ? (p.tile.unit >= 4 ? 1 : 0) : cd.order);
+        const std::string sig = describe(p);
         if (std::find(seen.begin(), seen.end(), sig) != seen.end()) continue;
         seen.push_back(sig);
         std::vector<float> ts;
