@@ -1391,6 +1391,61 @@ RR_HD void write_ragged(const TileArgs& a, const TileCtx& t, const uint8_t* lds,
     }
 }
 
+// Ragged write of 1- and 2-byte units from padded LDS rows: an item is one 16-byte
+// vector of GA = 4 / U neighbouring output rows (or one unit of each past the last
+// whole vector).  The rows' units lie side by side in LDS, so the item reads one
+// word per input row and transposes in registers: 16 word reads and 32 byte
+// permutes for 64 bytes of output (U = 1), where gathering each row by itself took
+// 64 byte reads and 60 shifts and ors.
+template <int U, bool S>
+RR_HD void write_ragged_narrow(const TileArgs& a, const TileCtx& t, const uint8_t* lds, uint32_t tid) {
+    constexpr uint32_t EPV = 16 / U, GA = 4 / U;
+    constexpr int RG = rot_group<U, 1>();   // == EPV: one output vector's rows share a rotation
+    const uint32_t rowbytes = t.TBv * U;
+    const uint32_t nfull = rowbytes >> 4;
+    const uint32_t per = nfull + ((rowbytes & 15u) / U);
+    if (per == 0) return;
+    const uint32_t ngroups = (t.TAv + GA - 1) / GA;
+    for (RowWalk w(tid, per); w.row < ngroups; w.step()) {
+        const uint32_t ia = w.row * GA;
+        const bool vec = w.col < nfull;
+        const uint32_t q0 = vec ? w.col * EPV : nfull * EPV + (w.col - nfull);
+        const uint32_t base = lds_pos<RG>(a, q0, ia * U);
+        uint64_t dst[GA];
+#pragma unroll
+        for (uint32_t i = 0; i < GA; ++i)   // a row past the tile's last is never stored: any row's address will do
+            dst[i] = t.bout + row_out(a, ia + i < t.TAv ? ia + i : ia) + (uint64_t)q0 * U;
+        if (vec) {
+            uint32_t r[EPV][1], o[GA][4];
+#pragma unroll
+            for (uint32_t j = 0; j < EPV; ++j) sload<4>(lds + base + j * a.pitch, r[j]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if constexpr (U == 1) {
+                    xpose4x4_b8(r[4 * q][0], r[4 * q + 1][0], r[4 * q + 2][0], r[4 * q + 3][0], o[0][q], o[1][q],
+                                o[2][q], o[3][q]);
+                } else {
+                    o[0][q] = perm_b32(r[2 * q + 1][0], r[2 * q][0], 0x05040100u);
+                    o[1][q] = perm_b32(r[2 * q + 1][0], r[2 * q][0], 0x07060302u);
+                }
+            }
+            sched_fence();
+#pragma unroll
+            for (uint32_t i = 0; i < GA; ++i)
+                if (ia + i < t.TAv) gstore16u<S>(reinterpret_cast<uint8_t*>(dst[i]), o[i]);
+        } else {
+            uint32_t r[1];
+            sload<4>(lds + base, r);
+            sched_fence();
+#pragma unroll
+            for (uint32_t i = 0; i < GA; ++i) {
+                const uint32_t e[1] = {r[0] >> (8 * U * i)};
+                if (ia + i < t.TAv) gstore<U, S>(reinterpret_cast<uint8_t*>(dst[i]), e);
+            }
+        }
+    }
+}
+
 // Flat write: the tile's output rows are back to back (row_out(ia) = ia*TB*U),
 // so the whole tile is one contiguous byte range, written as 16-byte vectors
 // whose elements come from LDS across row boundaries, plus an element tail.
@@ -1542,7 +1597,7 @@ RR_HD void write_umt(const TileArgs& a, const TileCtx& t, const uint8_t* lds, ui
     }
 }
 
-template <int U, int G, bool S>
+template <int U, int G, bool S, bool NARROW>
 RR_HD void write_tile(const TileArgs& a, const TileCtx& t, const uint8_t* lds, uint32_t tid) {
     constexpr int W = U * G;
     constexpr int NW = NWords<W>::value;
@@ -1556,8 +1611,11 @@ RR_HD void write_tile(const TileArgs& a, const TileCtx& t, const uint8_t* lds, u
             return;
         }
         if (a.flags & TF_RAGGED_OUT) {
-            if (a.flags & TF_IN_SEG) write_ragged<U, S, true>(a, t, lds, tid);
-            else write_ragged<U, S, false>(a, t, lds, tid);
+            if (a.flags & TF_IN_SEG) { write_ragged<U, S, true>(a, t, lds, tid); return; }
+            if constexpr (U < 4 && NARROW) {
+                if (a.k == 1 && !(a.flags & TF_IN_FLAT)) { write_ragged_narrow<U, S>(a, t, lds, tid); return; }
+            }
+            write_ragged<U, S, false>(a, t, lds, tid);
             return;
         }
     }
@@ -1651,10 +1709,17 @@ RR_HD void write_tile(const TileArgs& a, const TileCtx& t, const uint8_t* lds, u
     }
 }
 
-template <int U, int G>
+// NARROW: the kernel holds the word-wise ragged write of 1- and 2-byte units (the
+// single-launch G = 1 kernels leave it to k_tile_ragged).
+template <int U, int G, bool NARROW = true>
 RR_HD void write_phase(const TileArgs& a, const TileCtx& t, const uint8_t* lds, uint32_t tid) {
-    if (a.flags & TF_ST_CACHED) write_tile<U, G, false>(a, t, lds, tid);
-    else write_tile<U, G, true>(a, t, lds, tid);
+    if (a.flags & TF_ST_CACHED) write_tile<U, G, false, NARROW>(a, t, lds, tid);
+    else write_tile<U, G, true, NARROW>(a, t, lds, tid);
+}
+
+// Whether a tile plan runs the ragged paths of 1- and 2-byte units on both sides.
+RR_HD bool ragged_narrow(const TileArgs& a) {
+    return a.unit < 4 && a.g == 1 && a.k == 1 && (a.flags & TF_RAGGED_IN) && (a.flags & TF_RAGGED_OUT);
 }
 
 // ----------------------------------------------------------------- batches

@@ -26,6 +26,8 @@
 //               16-byte operations even for 1- and 2-byte elements.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "rr_device.hpp"
 #include "rr_kernels.hpp"
 
@@ -123,10 +125,37 @@ __global__ __launch_bounds__(NT) void k_tile(const TileArgs a) {
     const TileCtx t = tile_decode(a, block_to_tile(a, blockIdx.x));
     read_dispatch<U, G>(a, t, smem, threadIdx.x);
     __syncthreads();
-    write_phase<U, G>(a, t, smem, threadIdx.x);
+    write_phase<U, G, false>(a, t, smem, threadIdx.x);
+}
+
+// Odd-shaped tiles of 1- and 2-byte units (ragged_narrow), a kernel of their own:
+// with the other G = 1 paths in one kernel the arguments of all of them do not fit
+// the scalar registers.
+template <int U>
+__global__ __launch_bounds__(NT) void k_tile_ragged(const TileArgs a) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    const TileCtx t = tile_decode(a, block_to_tile(a, blockIdx.x));
+    if (a.flags & TF_LD_CACHED) read_ragged<U, false>(a, t, smem, threadIdx.x);
+    else read_ragged<U, true>(a, t, smem, threadIdx.x);
+    __syncthreads();
+    if (a.flags & TF_ST_CACHED) write_ragged_narrow<U, false>(a, t, smem, threadIdx.x);
+    else write_ragged_narrow<U, true>(a, t, smem, threadIdx.x);
 }
 
 // ----------------------------------------------------------------- launch
+template <int U>
+static hipError_t launch_tile_ragged(const TileArgs& a, uint32_t grid, hipStream_t st) {
+    static bool attr_done = false;
+    if (!attr_done) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_tile_ragged<U>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 65536);
+        if (e != hipSuccess) return e;
+        attr_done = true;
+    }
+    hipLaunchKernelGGL(k_tile_ragged<U>, dim3(grid), dim3(NT), std::max(a.lds_bytes, a.lds_reserve), st, a);
+    return hipGetLastError();
+}
+
 template <int U, int G>
 static hipError_t launch_tile_ug(const TileArgs& a, uint32_t grid, hipStream_t st) {
     static bool attr_done = false;
@@ -136,11 +165,12 @@ static hipError_t launch_tile_ug(const TileArgs& a, uint32_t grid, hipStream_t s
         if (e != hipSuccess) return e;
         attr_done = true;
     }
-    hipLaunchKernelGGL((k_tile<U, G>), dim3(grid), dim3(NT), a.lds_bytes, st, a);
+    hipLaunchKernelGGL((k_tile<U, G>), dim3(grid), dim3(NT), std::max(a.lds_bytes, a.lds_reserve), st, a);
     return hipGetLastError();
 }
 
 static hipError_t launch_tile(const TileArgs& a, uint32_t grid, hipStream_t st) {
+    if (ragged_narrow(a)) return a.unit == 1 ? launch_tile_ragged<1>(a, grid, st) : launch_tile_ragged<2>(a, grid, st);
     switch (a.unit * 100 + a.g) {
         case 101: return launch_tile_ug<1, 1>(a, grid, st);
         case 102: return launch_tile_ug<1, 2>(a, grid, st);

@@ -233,7 +233,8 @@ struct TileArgs {
     uint32_t segpitch;        // TF_IN_SEG: LDS bytes from one segment to the next (multiple of 16)
     Magic mseg;               // TF_IN_SEG: divide by segrows
     uint32_t order_out;       // tiles walk the grid in output order (planning only)
-    uint32_t pad_;
+    uint32_t lds_reserve;     // LDS a single launch asks for beyond lds_bytes (0: none), to hold
+                              // back how many of its workgroups share a CU
     uint64_t table[RR_MAX_PLANES];
 };
 
