@@ -770,6 +770,32 @@ static rr_status finish_tile(TileArgs& a, int U, int G, int k, uint64_t row_alig
 
 constexpr int64_t ORDER_IN_NEAR = 48;
 
+// Workgroups per CU.  A CU holds eight tile workgroups; on large problems eight
+// times 256 tiles in flight spread their lines over so many DRAM rows (and, where
+// tiles share lines, over so much L2) that four run faster: asking for 40 KiB of a
+// CU's 160 KiB of LDS holds the launch there.  Measured, eight -> four, us:
+// 16384^2 of 8 bytes 800 -> 785, 512 x 512 x 256 under (2,1,0) of 4 bytes 101.5 ->
+// 98.6, under (1,2,0) of 16 bytes 353 -> 339; sharing lines: 8193 x 8195 of 4 bytes
+// 139 -> 128, of 16 bytes 468 -> 433, 209 x 1169374 of 1 byte 185 -> 120.  Left at
+// eight: tiles well under 16 KiB or with short rows, whose latency needs the waves
+// (23-element rows of 4 bytes 164 -> 208); tiles that hold a side whole, which read
+// or write one long run (509 x 29 x 3388 of 8 bytes 153 -> 173); grids of few tiles
+// per CU, whose last wave would be emptier (28 MiB: 17.1 -> 18.3); aligned tiles of
+// 2 bytes, and of 4 bytes in diagonal order (0 to -4 %).  Odd 2-byte tiles of 8
+// to 14 KiB stay between, at five (6 x 36 x 236 x 629 x 13 under (3,0,1,4,2): 485 us
+// at eight, 426 at five; 227 x 112 x 631 x 23 under (3,1,2,0): 418 and 454).
+constexpr uint32_t FOUR_PER_CU = 40960, FIVE_PER_CU = 32768;
+static uint32_t tile_reserve(const TileArgs& a, const TileOptions& opt) {
+    if (opt.rows_only || a.ntiles < 8192 || (a.flags & TF_STACK)) return 0;
+    const bool share = (a.flags & TF_XCD) != 0;
+    const bool full = a.lds_bytes >= 14336 && (uint64_t)a.TA * a.R >= 128 && (uint64_t)a.TB * a.R >= 128;
+    if (!full)
+        return share && a.unit == 2 && a.lds_bytes >= 8192 && (a.flags & TF_RAGGED_IN) && (a.flags & TF_RAGGED_OUT) ? FIVE_PER_CU : 0;
+    if (a.grid_aO < 0 || a.grid_bO < 0) return 0;
+    if (!share && (a.unit == 2 || (a.unit == 4 && (a.flags & TF_DIAG)))) return 0;
+    return FOUR_PER_CU;
+}
+
 // Built-in diagonal tile order: 2-D transposes of 1-8-byte elements whose rows
 // are a power of two of at least 4 KiB on both sides.  Concurrent tiles then
 // start on rows 2^k bytes apart, which the HBM3E address hashing still piles
@@ -1135,6 +1161,7 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
         build_grid(a.order_out);
     }
     if (a.ngrid >= 2 && (opt.diag == 1 || (opt.diag == -1 && diag_by_default(c)))) a.flags |= TF_DIAG;
+    a.lds_reserve = tile_reserve(a, opt);
     p->grid = a.ntiles;
     p->bytes = (uint64_t)c.total_bytes;
     return RR_OK;
