@@ -151,18 +151,40 @@ def check(status: int) -> int:
     return status
 
 
+_I64 = [ctypes.c_int64 * max(1, n) for n in range(RR_MAX_DIMS + 1)]
+_I32 = [ctypes.c_int * max(1, n) for n in range(RR_MAX_DIMS + 1)]
+
+
 def _i64(seq):
-    return (ctypes.c_int64 * max(1, len(seq)))(*[int(x) for x in seq])
+    n = len(seq)
+    return (_I64[n] if n <= RR_MAX_DIMS else ctypes.c_int64 * n)(*[int(x) for x in seq])
 
 
 def _i32(seq):
-    return (ctypes.c_int * max(1, len(seq)))(*[int(x) for x in seq])
+    n = len(seq)
+    return (_I32[n] if n <= RR_MAX_DIMS else ctypes.c_int * n)(*[int(x) for x in seq])
+
+
+_raw_stream = None   # (current device, device -> hipStream_t of its current stream)
+
+
+def _current_stream() -> int:
+    """torch.cuda.current_stream().cuda_stream without building the Stream object,
+    which takes longer (2.9 us) than the library's launch of a small transpose."""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is None:
+            raw = lambda device: torch.cuda.current_stream(device).cuda_stream
+        _raw_stream = (torch.cuda.current_device, raw)
+    device, raw = _raw_stream
+    return raw(device())
 
 
 def _stream_handle(stream) -> int:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
