@@ -930,18 +930,23 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
         const int64_t rowb = innerA * t[aO] * R;
         return !umt && G == 1 && U < 16 && t[aO] == d[aO] && b1 == r - 1 - nA && sinb[b1] == rowb && rowb < SEG_ROW_BYTES;
     };
+    // Segments fill a tile to the byte, so a small problem would leave the chip idle:
+    // smaller tiles there, for about two workgroups per CU (crop of 0.6 MB, 4-byte
+    // records: 38 full tiles 10.4 us).
+    const int64_t seg_lds = std::max<int64_t>(2048, std::min<int64_t>(soft_lds, c.total_bytes / 512));
     if (back_to_back() && nB > 1) {
         const int64_t segb = (t[b1] * innerA * t[aO] * R + 15) / 16 * 16, per = innerB / t[b1] * segb;
-        const int64_t fit = std::max<int64_t>(1, soft_lds / per);
+        const int64_t fit = std::max<int64_t>(1, seg_lds / per);
         if (t[bO] > fit) t[bO] = fit;
         t[bO] = cdiv(d[bO], cdiv(d[bO], t[bO]));   // evened out
     }
     for (int guard = 0; guard < 64; ++guard) {
         int64_t TA = innerA * t[aO], TB = innerB * t[bO];
         int64_t bytes = TB * ((TA * R + 15) / 16 * 16);
-        if (back_to_back())
+        const bool packed = back_to_back();
+        if (packed)
             bytes = nB == 1 ? (TB * TA * R + 15) / 16 * 16 : TB / t[b1] * ((t[b1] * TA * R + 15) / 16 * 16);
-        if (bytes <= soft_lds) break;
+        if (bytes <= (packed ? seg_lds : soft_lds)) break;
         int64_t stepA = nA == 1 ? G : 1, stepB = nB == 1 ? G : 1;
         bool canA = t[aO] > stepA, canB = t[bO] > stepB;
         if (!canA && !canB) {
