@@ -1717,6 +1717,46 @@ RR_HD void write_phase(const TileArgs& a, const TileCtx& t, const uint8_t* lds, 
     else write_tile<U, G, true, NARROW>(a, t, lds, tid);
 }
 
+// Segment tiles of records of N units, N = 2..8 (pixels to planes): an item is 16 / U
+// consecutive records of a segment, N aligned 16-byte LDS reads split in registers
+// (weave_regs) into one vector of each of the N output rows; the records past a
+// segment's last whole group move unit by unit, one unit per thread.
+template <int U, int N, bool S>
+RR_HD void write_split(const TileArgs& a, const TileCtx& t, const uint8_t* lds, uint32_t tid) {
+    constexpr uint32_t E = 16 / U;
+    const uint32_t rows = umin(a.segrows, t.TBv), nseg = mdiv(t.TBv + a.segrows - 1, a.mseg);
+    const uint32_t ngroup = rows / E, rem = rows - ngroup * E;
+    uint64_t out[N];
+#pragma unroll
+    for (int c = 0; c < N; ++c) out[c] = t.bout + row_out(a, (uint32_t)c);
+    if (ngroup)
+        for (RowWalk w(tid, ngroup); w.row < nseg; w.step()) {
+            uint32_t in[N][4], o[N][4];
+            const uint8_t* p = lds + w.row * a.segpitch + w.col * (16u * N);
+#pragma unroll
+            for (int k = 0; k < N; ++k) sload<16>(p + 16 * k, in[k]);
+            weave_regs<U, N, true>(in, o);
+            const uint64_t at = ((uint64_t)w.row * a.segrows + w.col * E) * U;
+#pragma unroll
+            for (int c = 0; c < N; ++c) gstore16u<S>(reinterpret_cast<uint8_t*>(out[c] + at), o[c]);
+        }
+    if (rem)
+        for (RowWalk w(tid, rem * N); w.row < nseg; w.step()) {
+            const uint32_t c = w.col / rem, i = ngroup * E + (w.col - c * rem);
+            uint32_t e[NWords<U>::value];
+            sload<U>(lds + w.row * a.segpitch + (i * N + c) * U, e);
+            const uint64_t q = t.bout + row_out(a, c) + ((uint64_t)w.row * a.segrows + i) * U;
+            gstore_u<U, S>(reinterpret_cast<uint8_t*>(q), e);
+        }
+}
+
+// Whether a tile plan is one for write_split: whole records of 2..8 units read as
+// segments, written through the caches (its kernels hold no other flavour).
+RR_HD bool tile_split(const TileArgs& a) {
+    return (a.flags & TF_IN_SEG) && (a.flags & TF_RAGGED_OUT) && (a.flags & TF_ST_CACHED) && !(a.flags & TF_LD_CACHED) &&
+           a.unit <= 8 && a.k == 1 && a.g == 1 && a.grid_aO < 0 && a.TA >= 2 && a.TA <= 8;
+}
+
 // Whether a tile plan runs the ragged paths of 1- and 2-byte units on both sides.
 RR_HD bool ragged_narrow(const TileArgs& a) {
     return a.unit < 4 && a.g == 1 && a.k == 1 && (a.flags & TF_RAGGED_IN) && (a.flags & TF_RAGGED_OUT);

@@ -11,6 +11,9 @@ namespace rr {
 // Enqueue the kernel a plan selects on `st`.  Returns the launch status.
 hipError_t launch_plan(const Plan& p, hipStream_t st);
 
+// Enqueue the record-splitting tile kernel for a plan that tile_split accepts.
+hipError_t launch_tile_split(const TileArgs& a, uint32_t grid, hipStream_t st);
+
 // Enqueue the 2-D stencil kernel for radius 1..4 and shape 0/1.
 hipError_t launch_stencil(const StencilArgs& a, hipStream_t st);
 

@@ -47,6 +47,20 @@ static void write_file(const std::string& path, const uint8_t* p, size_t n) {
     f.write(reinterpret_cast<const char*>(p), (std::streamsize)n);
 }
 
+template <int U>
+static bool write_split_n(const TileArgs& a, const TileCtx& t, const uint8_t* lds, uint32_t tid) {
+    switch (a.TA) {
+        case 2: write_split<U, 2, false>(a, t, lds, tid); return true;
+        case 3: write_split<U, 3, false>(a, t, lds, tid); return true;
+        case 4: write_split<U, 4, false>(a, t, lds, tid); return true;
+        case 5: write_split<U, 5, false>(a, t, lds, tid); return true;
+        case 6: write_split<U, 6, false>(a, t, lds, tid); return true;
+        case 7: write_split<U, 7, false>(a, t, lds, tid); return true;
+        case 8: write_split<U, 8, false>(a, t, lds, tid); return true;
+    }
+    return false;
+}
+
 template <int U, int G>
 static void run_tile_ug(const TileArgs& a, uint32_t grid) {
     std::vector<uint8_t> seen(grid, 0);
@@ -57,7 +71,15 @@ static void run_tile_ug(const TileArgs& a, uint32_t grid) {
         std::memset(lds, 0xA5, a.lds_bytes);
         const TileCtx t = tile_decode(a, tile);
         for (uint32_t tid = 0; tid < (uint32_t)NT; ++tid) read_dispatch<U, G>(a, t, lds, tid);
-        for (uint32_t tid = 0; tid < (uint32_t)NT; ++tid) write_phase<U, G>(a, t, lds, tid);
+        for (uint32_t tid = 0; tid < (uint32_t)NT; ++tid) {
+            if constexpr (G == 1 && U < 16) {   // as launch_tile picks the kernel
+                if (tile_split(a) && a.lds_bytes <= 32768) {
+                    if (!write_split_n<U>(a, t, lds, tid)) std::abort();
+                    continue;
+                }
+            }
+            write_phase<U, G>(a, t, lds, tid);
+        }
         delete[] lds;
     }
 }

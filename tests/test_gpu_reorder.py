@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 import rr_synth
-from tests.test_emulated_kernels import REORDER_CASES, SELECT_CASES, random_boxes
+from tests.test_emulated_kernels import REORDER_CASES, SEG_READ_CASES, SELECT_CASES, random_boxes
 
 pytestmark = pytest.mark.gpu
 
@@ -52,6 +52,19 @@ def test_reorder_cases(rr):
 def test_reorder_random_boxes(rr):
     for i, (d, b, r, o, e) in enumerate(random_boxes(91, 150)):
         check(rr, d, b, r, o, e, 11100 + i)
+
+
+def test_reorder_segments_and_record_splits(rr):
+    """Short rows read as segments, at odd pointers too, and crops of records of 2-8
+    units of 1-8 bytes split into planes: segments of whole vectors, with a tail,
+    shorter than a vector, and several tiles with a partial last one."""
+    for i, (d, b, r, o, e, _) in enumerate(SEG_READ_CASES):
+        check(rr, d, b, r, o, e, 11300 + i)
+        check(rr, d, b, r, o, e, 11330 + i, soff=e, doff=3)
+    for n in range(2, 9):
+        for j, e in enumerate((1, 2, 4, 8)):
+            w = (17, 32, 67, 9)[(n + j) % 4]
+            check(rr, (3, 150, 90, n), (0, 7, 5, 0), (3, 131, w, n), (0, 3, 1, 2), e, 11400 + 10 * n + j)
 
 
 def test_reorder_large_boxes(rr):
