@@ -431,7 +431,7 @@ rr_status rr_interlace_describe(const void* flat, const void* const* planes, int
  * input and output sides of the tiled kernel (0 = built-in choice, max 4096),
  * the order in which tiles are assigned to workgroups (flags:
  * RR_TILE_ORDER_OUT / RR_TILE_ORDER_IN, neither = built-in choice by element
- * size), a cap on the register micro-tile edge G (RR_TILE_MAX_G(g), g one of
+ * size and by how far apart the tiles are that share lines), a cap on the register micro-tile edge G (RR_TILE_MAX_G(g), g one of
  * 1, 2, 4, 8, 16; 0 = no cap) and the LDS size tiles are shrunk to
  * (RR_TILE_KIB(k), 4..64 KiB; 0 = 16); RR_TILE_XCD hands each of the 8 XCDs a
  * contiguous range of tiles instead of every 8th one, RR_TILE_NO_XCD never does

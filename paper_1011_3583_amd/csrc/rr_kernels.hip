@@ -152,7 +152,7 @@ static hipError_t launch_tile_ragged(const TileArgs& a, uint32_t grid, hipStream
         if (e != hipSuccess) return e;
         attr_done = true;
     }
-    hipLaunchKernelGGL(k_tile_ragged<U>, dim3(grid), dim3(NT), std::max(a.lds_bytes, a.lds_reserve), st, a);
+    hipLaunchKernelGGL(k_tile_ragged<U>, dim3(grid), dim3(NT), launch_lds(a), st, a);
     return hipGetLastError();
 }
 
@@ -165,7 +165,7 @@ static hipError_t launch_tile_ug(const TileArgs& a, uint32_t grid, hipStream_t s
         if (e != hipSuccess) return e;
         attr_done = true;
     }
-    hipLaunchKernelGGL((k_tile<U, G>), dim3(grid), dim3(NT), std::max(a.lds_bytes, a.lds_reserve), st, a);
+    hipLaunchKernelGGL((k_tile<U, G>), dim3(grid), dim3(NT), launch_lds(a), st, a);
     return hipGetLastError();
 }
 

@@ -784,16 +784,15 @@ constexpr int64_t ORDER_IN_NEAR = 48;
 // 2 bytes, and of 4 bytes in diagonal order (0 to -4 %).  Odd 2-byte tiles of 8
 // to 14 KiB stay between, at five (6 x 36 x 236 x 629 x 13 under (3,0,1,4,2): 485 us
 // at eight, 426 at five; 227 x 112 x 631 x 23 under (3,1,2,0): 418 and 454).
-constexpr uint32_t FOUR_PER_CU = 40960, FIVE_PER_CU = 32768;
 static uint32_t tile_reserve(const TileArgs& a, const TileOptions& opt) {
     if (opt.rows_only || a.ntiles < 8192 || (a.flags & TF_STACK)) return 0;
     const bool share = (a.flags & TF_XCD) != 0;
     const bool full = a.lds_bytes >= 14336 && (uint64_t)a.TA * a.R >= 128 && (uint64_t)a.TB * a.R >= 128;
     if (!full)
-        return share && a.unit == 2 && a.lds_bytes >= 8192 && (a.flags & TF_RAGGED_IN) && (a.flags & TF_RAGGED_OUT) ? FIVE_PER_CU : 0;
+        return share && a.unit == 2 && a.lds_bytes >= 8192 && (a.flags & TF_RAGGED_IN) && (a.flags & TF_RAGGED_OUT) ? TF_FIVE_PER_CU : 0;
     if (a.grid_aO < 0 || a.grid_bO < 0) return 0;
     if (!share && (a.unit == 2 || (a.unit == 4 && (a.flags & TF_DIAG)))) return 0;
-    return FOUR_PER_CU;
+    return TF_FOUR_PER_CU;
 }
 
 // Built-in diagonal tile order: 2-D transposes of 1-8-byte elements whose rows
@@ -932,13 +931,21 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
     };
     // Segments fill a tile to the byte, so a small problem would leave the chip idle:
     // smaller tiles there, for about two workgroups per CU (crop of 0.6 MB, 4-byte
-    // records: 38 full tiles 10.4 us).
-    const int64_t seg_lds = std::max<int64_t>(2048, std::min<int64_t>(soft_lds, c.total_bytes / 512));
+    // records: 38 full tiles 10.4 us).  Shapes asked for stay, and
+    // so do batches' (their other jobs fill the chip).
+    const int64_t seg_lds =
+        opt.in_row_bytes || opt.out_row_bytes ? soft_lds : std::max<int64_t>(2048, std::min<int64_t>(soft_lds, c.total_bytes / 512));
     if (back_to_back() && nB > 1) {
         const int64_t segb = (t[b1] * innerA * t[aO] * R + 15) / 16 * 16, per = innerB / t[b1] * segb;
         const int64_t fit = std::max<int64_t>(1, seg_lds / per);
         if (t[bO] > fit) t[bO] = fit;
         t[bO] = cdiv(d[bO], cdiv(d[bO], t[bO]));   // evened out
+    }
+    // Whether a problem is handled does not depend on which read its tiles get: where
+    // not even the smallest tile fits with padded rows, packed ones are refused too.
+    if (back_to_back() && innerB * ((innerA * R + 15) / 16 * 16) > opt.max_lds) {
+        *why = "cannot fit a tile in LDS";
+        return RR_ERR_UNSUPPORTED;
     }
     for (int guard = 0; guard < 64; ++guard) {
         int64_t TA = innerA * t[aO], TB = innerB * t[bO];
@@ -1085,10 +1092,10 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
     a.src = src; a.dst = dst;
     // tile grid
     auto tiles_along = [&](int s) { return inA[s] || inB[s] || s == cax ? cdiv(d[s], t[s]) : d[s]; };
-    auto build_grid = [&](bool order_out) {
+    auto build_grid = [&](bool by_out) {
         a.ngrid = 0; a.grid_aO = -1; a.grid_bO = -1; a.grid_cO = -1;
         for (int oi = 0; oi < r; ++oi) {
-            const int s = order_out ? pm[oi] : oi;
+            const int s = by_out ? pm[oi] : oi;
             const int64_t n = tiles_along(s);
             if (n <= 1) continue;
             const int g = a.ngrid++;
@@ -1109,8 +1116,8 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
     // Tiles that share no lines: 4..16-byte elements are walked in output order
     // (neighbouring workgroups then write neighbouring output segments); 1- and
     // 2-byte elements keep input order, which measured slightly faster for them.
-    a.order_out = opt.order_out < 0 ? U >= 4 : opt.order_out != 0;
-    build_grid(a.order_out);
+    bool order_out = opt.order_out < 0 ? U >= 4 : opt.order_out != 0;
+    build_grid(order_out);
     a.aO_len = (uint32_t)d[aO]; a.aO_t = (uint32_t)t[aO];
     a.bO_len = (uint32_t)d[bO]; a.bO_t = (uint32_t)t[bO];
     if (cax >= 0) { a.cO_len = (uint32_t)d[cax]; a.cO_t = (uint32_t)t[cax]; }
@@ -1146,7 +1153,7 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
     // line (256013 x 1043 of 2 bytes, far_in 9), output order up to 2.1x above it
     // (9744 x 18176 of 2 bytes, 142: 1.5x; 107 x 3135674: 1.85x).
     if (opt.order_out < 0 && (a.flags & TF_XCD)) {
-        auto distance = [&](bool order_out, bool out_side) {
+        auto distance = [&](bool by_out, bool out_side) {
             // the fastest axis, on that side, along which there are several tiles
             int x = -1;
             for (int j = r - 1; j >= 0 && x < 0; --j) {
@@ -1155,18 +1162,19 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
             }
             int64_t dist = 1;
             for (int oi = r - 1; oi >= 0; --oi) {
-                const int s = order_out ? pm[oi] : oi;
+                const int s = by_out ? pm[oi] : oi;
                 if (s == x) break;
                 dist *= tiles_along(s);
             }
             return dist;
         };
         const int64_t far_in = distance(false, true), far_out = distance(true, false);
-        a.order_out = !(far_in < far_out && far_in <= ORDER_IN_NEAR);
-        build_grid(a.order_out);
+        order_out = !(far_in < far_out && far_in <= ORDER_IN_NEAR);
+        build_grid(order_out);
     }
     if (a.ngrid >= 2 && (opt.diag == 1 || (opt.diag == -1 && diag_by_default(c)))) a.flags |= TF_DIAG;
-    a.lds_reserve = tile_reserve(a, opt);
+    if (order_out) a.flags |= TF_ORDER_OUT;
+    a.flags |= tile_reserve(a, opt);
     p->grid = a.ntiles;
     p->bytes = (uint64_t)c.total_bytes;
     return RR_OK;
@@ -1398,7 +1406,7 @@ std::string describe(const Plan& p) {
         o << " unit=" << a.unit << " g=" << a.g << " k=" << a.k << " TA=" << a.TA << " TB=" << a.TB
           << " nA=" << a.nA << " nB=" << a.nB << " win=" << a.win << " pitch=" << a.pitch
           << " lds=" << a.lds_bytes << " ntiles=" << a.ntiles << " ngrid=" << a.ngrid
-          << " tc=" << a.cO_t << " flags=" << a.flags << " order=" << (a.order_out ? "out" : "in");
+          << " tc=" << a.cO_t << " flags=" << a.flags << " order=" << (a.flags & TF_ORDER_OUT ? "out" : "in");
     }
     return o.str();
 }

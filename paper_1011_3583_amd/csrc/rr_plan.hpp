@@ -183,6 +183,9 @@ enum TileFlags : uint32_t {
     TF_IN_SEG = 8192u,      // short input rows back to back in segments of segrows rows (the
                             // innermost B axis), each segment read as one range of any alignment;
                             // LDS rows unpadded within a segment
+    TF_ORDER_OUT = 16384u,  // the tile grid is walked in output order (planning only)
+    TF_FOUR_PER_CU = 32768u,// a single launch reserves LDS so that at most four of its
+    TF_FIVE_PER_CU = 65536u,// (at most five) workgroups share a CU
 };
 
 struct TileArgs {
@@ -224,19 +227,30 @@ struct TileArgs {
     uint32_t g;               // G
     int32_t grid_cO;          // stacked: grid index of the C axis (-1: none)
     uint32_t cO_len, cO_t;    // extent of C and sub-tiles per tile (cO_t = 1 unless stacked)
-    uint32_t msub;            // stacked: bytes of one sub-tile (TA * TB * R)
-    uint32_t msubp;           // stacked: LDS bytes per sub-tile (msub if back to back in
+    // a stacked tile is never read as segments: the two share their fields, so that a
+    // batch's job table holds as many jobs as without segments
+    union {
+        uint32_t msub;        // stacked: bytes of one sub-tile (TA * TB * R)
+        uint32_t segrows;     // TF_IN_SEG: rows per segment
+    };
+    union {
+        uint32_t msubp;       // stacked: LDS bytes per sub-tile (msub if back to back in
                               // the input, else msub rounded up to 16)
-    Magic msubel;             // stacked: divide by TA * TB
+        uint32_t segpitch;    // TF_IN_SEG: LDS bytes from one segment to the next (multiple of 16)
+    };
+    union {
+        Magic msubel;         // stacked: divide by TA * TB
+        Magic mseg;           // TF_IN_SEG: divide by segrows
+    };
     uint64_t sinC, soutC;     // stacked: byte stride of C in input and output
-    uint32_t segrows;         // TF_IN_SEG: rows per segment
-    uint32_t segpitch;        // TF_IN_SEG: LDS bytes from one segment to the next (multiple of 16)
-    Magic mseg;               // TF_IN_SEG: divide by segrows
-    uint32_t order_out;       // tiles walk the grid in output order (planning only)
-    uint32_t lds_reserve;     // LDS a single launch asks for beyond lds_bytes (0: none), to hold
-                              // back how many of its workgroups share a CU
     uint64_t table[RR_MAX_PLANES];
 };
+
+// LDS that a single launch of a tile plan asks for.
+inline uint32_t launch_lds(const TileArgs& a) {
+    const uint32_t reserve = a.flags & TF_FOUR_PER_CU ? 40960u : a.flags & TF_FIVE_PER_CU ? 32768u : 0u;
+    return a.lds_bytes > reserve ? a.lds_bytes : reserve;
+}
 
 struct TileOptions {
     int in_row_bytes = 0;   // 0 = default
