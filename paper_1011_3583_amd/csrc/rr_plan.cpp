@@ -780,7 +780,8 @@ constexpr int64_t ORDER_IN_NEAR = 48;
 // eight: tiles well under 16 KiB or with short rows, whose latency needs the waves
 // (23-element rows of 4 bytes 164 -> 208); tiles that hold a side whole, which read
 // or write one long run (509 x 29 x 3388 of 8 bytes 153 -> 173); grids of few tiles
-// per CU, whose last wave would be emptier (28 MiB: 17.1 -> 18.3); aligned tiles of
+// per CU, whose last wave would be emptier (28 MiB: 17.1 -> 18.3; 9184 tiles that share no
+// lines, 240 x 36736 of 16 bytes, 52.3 -> 53.2, while 16384 gain above); aligned tiles of
 // 2 bytes, and of 4 bytes in diagonal order (0 to -4 %).  Odd 2-byte tiles of 8
 // to 14 KiB stay between, at five (6 x 36 x 236 x 629 x 13 under (3,0,1,4,2): 485 us
 // at eight, 426 at five; 227 x 112 x 631 x 23 under (3,1,2,0): 418 and 454).
@@ -791,6 +792,7 @@ static uint32_t tile_reserve(const TileArgs& a, const TileOptions& opt) {
     if (!full)
         return share && a.unit == 2 && a.lds_bytes >= 8192 && (a.flags & TF_RAGGED_IN) && (a.flags & TF_RAGGED_OUT) ? TF_FIVE_PER_CU : 0;
     if (a.grid_aO < 0 || a.grid_bO < 0) return 0;
+    if (!share && a.ntiles < 16384) return 0;
     if (!share && (a.unit == 2 || (a.unit == 4 && (a.flags & TF_DIAG)))) return 0;
     return TF_FOUR_PER_CU;
 }
