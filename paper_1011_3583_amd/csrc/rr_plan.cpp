@@ -933,8 +933,10 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
     };
     // Segments fill a tile to the byte, so a small problem would leave the chip idle:
     // smaller tiles there, for about two workgroups per CU (crop of 0.6 MB, 4-byte
-    // records: 38 full tiles 10.4 us).  Shapes asked for stay, and
-    // so do batches' (their other jobs fill the chip).
+    // records: 38 full tiles 10.4 us).  Only B is split for it: a tile of part of
+    // each record has no segments to read (300 x 300 RGB floats 6.4 -> 5.0 us, 500 x
+    // 690 RGB bytes 7.7 -> 5.1).  Shapes asked for stay, and so do batches' (their
+    // other jobs fill the chip).
     const int64_t seg_lds =
         opt.in_row_bytes || opt.out_row_bytes ? soft_lds : std::max<int64_t>(2048, std::min<int64_t>(soft_lds, c.total_bytes / 512));
     if (back_to_back() && nB > 1) {
@@ -958,6 +960,10 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
         if (bytes <= (packed ? seg_lds : soft_lds)) break;
         int64_t stepA = nA == 1 ? G : 1, stepB = nB == 1 ? G : 1;
         bool canA = t[aO] > stepA, canB = t[bO] > stepB;
+        if (packed && bytes <= soft_lds) {   // records stay whole
+            if (!canB) break;
+            canA = false;
+        }
         if (!canA && !canB) {
             if (bytes <= opt.max_lds) break;
             *why = "cannot fit a tile in LDS";

@@ -360,6 +360,21 @@ def test_emu_short_rows_read_as_segments():
             assert np.array_equal(out[c], np.ascontiguousarray(ref[:, c]).reshape(-1)), (j["n"], c)
 
 
+def test_emu_small_crops_keep_whole_records():
+    """A small crop whose single line is longer than the tile size that fills the chip:
+    the tile keeps whole records (three units, read as segments) and only its lines
+    are split over workgroups."""
+    cases = [((1, 320, 320, 3), (0, 10, 10, 0), (1, 300, 300, 3), 4), ((1, 520, 700, 3), (0, 10, 5, 0), (1, 500, 690, 3), 1),
+             ((1, 90, 700, 3), (0, 3, 5, 0), (1, 80, 690, 3), 2), ((2, 30, 250, 5), (0, 3, 5, 0), (2, 20, 240, 5), 4)]
+    jobs = [_reorder_job(d, b, r, (0, 3, 1, 2), e, 8950 + i) for i, (d, b, r, e) in enumerate(cases)]
+    for j, (st, out) in zip(jobs, emu_runner.run(jobs)):
+        assert st.startswith("ok"), (j["dims"], st)
+        ref = oracle.reorder_slice(j["input"], j["dims"], j["base"], j["range"], j["order"], j["esize"])
+        assert np.array_equal(out, ref), (j["dims"], st)
+        f = dict(kv.split("=", 1) for kv in st.split() if "=" in kv)
+        assert int(f["TA"]) == j["dims"][3] and int(f["flags"]) & 8192, (j["dims"], st)
+
+
 SELECT_CASES = [
     # one channel of interleaved records: (dims, base, range, order, element bytes)
     ((64, 96, 4), (0, 0, 2), (64, 96, 1), (0, 1), 1),          # RGBA plane, fused to one row
