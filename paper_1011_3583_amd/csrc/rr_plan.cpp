@@ -938,7 +938,7 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
     // 690 RGB bytes 7.7 -> 5.1).  Shapes asked for stay, and so do batches' (their
     // other jobs fill the chip).
     const int64_t seg_lds =
-        opt.in_row_bytes || opt.out_row_bytes ? soft_lds : std::max<int64_t>(2048, std::min<int64_t>(soft_lds, c.total_bytes / 512));
+        opt.in_row_bytes || opt.out_row_bytes || opt.tile_kib ? soft_lds : std::max<int64_t>(2048, std::min<int64_t>(soft_lds, c.total_bytes / 512));
     if (back_to_back() && nB > 1) {
         const int64_t segb = (t[b1] * innerA * t[aO] * R + 15) / 16 * 16, per = innerB / t[b1] * segb;
         const int64_t fit = std::max<int64_t>(1, seg_lds / per);

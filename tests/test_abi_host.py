@@ -560,3 +560,17 @@ def test_diagonal_order_by_default():
             rr.check(rr.lib().rr_set_tile_override(0, 0, 128 | (1 << 30)))
     finally:
         rr.set_tile_override()
+
+
+def test_requested_tile_size_holds_for_small_crops():
+    """Small crops of short records take smaller tiles by default; a tile size asked for
+    with the override is the size tiles are shrunk to, whatever the problem's size."""
+    args = ((16, 100, 80, 3), (0, 4, 6, 0), (16, 90, 60, 3), (0, 3, 1, 2), 1, 1 << 40, 1 << 41)
+    try:
+        assert int(rr.reorder_describe(*args)["lds"]) <= 4096
+        for kib in (8, 16, 32):
+            rr.set_tile_override(tile_kib=kib)
+            lds = int(rr.reorder_describe(*args)["lds"])
+            assert kib * 512 < lds <= kib * 1024, (kib, lds)
+    finally:
+        rr.set_tile_override()
