@@ -532,6 +532,23 @@ static bool plan_select(uint64_t dst, uint64_t src, const Canon& c, Plan* p) {
 // (longer ones fill padded, rotated LDS rows without bank conflicts).
 constexpr int64_t SEG_ROW_BYTES = 64;
 
+// Whether segments beat padded rows.  Records of 2-8 units are split in registers
+// (write_split) and elements of several units go unit by unit either way: always.
+// Other segment tiles are written by lanes that each gather 16 / U rows, the lanes of
+// a wave 16 / U * rowb bytes apart in LDS: where that is a multiple of 128 bytes they
+// read one or two of the 64 banks.  Rows of whole 16-byte vectors are also the ones
+// that a padded read needs no unit loop for.  MI355X, segments against padded rows,
+// us, crops of 61 x 401 x 301 records of C bytes: C = 9 37 / 120, 17 71 / 83, 28 119 /
+// 203, 47 197 / 278, but 16 183 / 57, 32 287 / 92, 40 353 / 189, 48 426 / 127; of C
+// 2-byte units: 15 112 / 211, but 16 170 / 113, 24 247 / 137.  24-byte rows of bytes
+// gain over several B axes ((3,1,0,2) of 63 x 801 x 19 records 27 / 34) and lose over
+// one (22 / 14).
+static bool seg_pays(int U, int k, int64_t TA, int64_t rowb, int nB, bool out_table) {
+    if (k > 1 || (TA >= 2 && TA <= 8 && !out_table)) return true;
+    if (rowb % 16 == 0) return false;
+    return (16 / U * rowb) % 128 != 0 || (rowb == 24 && nB > 1);
+}
+
 static int default_row_bytes(int U, bool in_side) {
     switch (U) {
         case 1: return 128;
@@ -929,7 +946,8 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
     const int64_t soft_lds = std::min<int64_t>(soft_bytes, opt.max_lds);
     auto back_to_back = [&]() {
         const int64_t rowb = innerA * t[aO] * R;
-        return !umt && G == 1 && U < 16 && t[aO] == d[aO] && b1 == r - 1 - nA && sinb[b1] == rowb && rowb < SEG_ROW_BYTES;
+        return !umt && G == 1 && U < 16 && t[aO] == d[aO] && b1 == r - 1 - nA && sinb[b1] == rowb && rowb < SEG_ROW_BYTES &&
+               seg_pays(U, k, innerA * t[aO], rowb, nB, false);
     };
     // Segments fill a tile to the byte, so a small problem would leave the chip idle:
     // smaller tiles there, for about two workgroups per CU (crop of 0.6 MB, 4-byte
@@ -1367,7 +1385,7 @@ static rr_status plan_interlace_tile(uint64_t flat, const uint64_t* planes, int 
         a.bO_len = (uint32_t)count; a.bO_t = (uint32_t)L;
         for (int c = 0; c < n; ++c) a.table[c] = planes[c];
         uint64_t ra = a.src | (uint64_t)(n * R);
-        rr_status st = finish_tile(a, U, G, k, ra, true, a.src, 0, a.TB, opt, why);
+        rr_status st = finish_tile(a, U, G, k, ra, true, a.src, 0, seg_pays(U, k, n, n * R, 1, true) ? a.TB : 0, opt, why);
         if (st != RR_OK) return st;
     }
     cache_policy(a, opt);

@@ -375,6 +375,35 @@ def test_emu_small_crops_keep_whole_records():
         assert int(f["TA"]) == j["dims"][3] and int(f["flags"]) & 8192, (j["dims"], st)
 
 
+@pytest.mark.parametrize("e", [1, 2, 4])
+def test_emu_segments_only_where_their_banks_spread(e):
+    """Rows of whole 16-byte vectors, and rows whose gather would stay on one or two LDS
+    banks, keep the padded read (crops, permutes and de-interlaces off a boundary, over
+    one B axis and several); rows around them read as segments.  All match the oracle."""
+    jobs, want = [], []
+    for c in sorted({9, 15, 16, 17, 24, 28, 31, 32, 33, 40, 47, 48, 56, 63, *range(9, 16)}):
+        row = c * e
+        if row >= 64:
+            continue
+        for nb, j in ((2, _reorder_job((2, 11, 13, c), (0, 1, 1, 0), (2, 9, 11, c), (0, 3, 1, 2), e, 9000 + c)),
+                      (2, _perm_job((5, 7, 9, c), (3, 1, 0, 2), e, 9100 + c)),
+                      (1, _perm_job((211, c), (1, 0), e, 9200 + c, src_off=e, dst_off=0))):
+            jobs.append(j)
+            want.append(row % 16 != 0 and (16 // e * row % 128 != 0 or (row == 24 and nb > 1)))
+    for j, w, (st, out) in zip(jobs, want, emu_runner.run(jobs)):
+        assert st.startswith("ok"), (j["dims"], st)
+        ref = (oracle.reorder_slice(j["input"], j["dims"], j["base"], j["range"], j["order"], e) if j["op"] == "reorder"
+               else oracle.permute(j["input"], j["dims"], j["perm"], e))
+        assert np.array_equal(out, ref), (j["dims"], st)
+        assert bool(int(st.split(" flags=")[1].split()[0]) & 8192) == w, (j["dims"], e, st)
+    planes = [dict(op="deinterlace", n=n, count=777, esize=e, off=e, input=rr_synth.random_bytes(9300 + n, n * 777 * e))
+              for n in (9, 12, 16) if n * e < 64]
+    for j, (st, out) in zip(planes, emu_runner.run(planes)):
+        assert st.startswith("ok"), st
+        assert bool(int(st.split(" flags=")[1].split()[0]) & 8192) == (j["n"] * e % 16 != 0), (j["n"], e, st)
+        assert all(np.array_equal(o, r) for o, r in zip(out, oracle.deinterlace(j["input"], j["n"], e))), (j["n"], e)
+
+
 SELECT_CASES = [
     # one channel of interleaved records: (dims, base, range, order, element bytes)
     ((64, 96, 4), (0, 0, 2), (64, 96, 1), (0, 1), 1),          # RGBA plane, fused to one row
