@@ -1750,18 +1750,6 @@ RR_HD void write_split(const TileArgs& a, const TileCtx& t, const uint8_t* lds, 
         }
 }
 
-// Whether a tile plan is one for write_split: whole records of 2..8 units read as
-// segments, written through the caches (its kernels hold no other flavour).
-RR_HD bool tile_split(const TileArgs& a) {
-    return (a.flags & TF_IN_SEG) && (a.flags & TF_RAGGED_OUT) && (a.flags & TF_ST_CACHED) && !(a.flags & TF_LD_CACHED) &&
-           a.unit <= 8 && a.k == 1 && a.g == 1 && a.grid_aO < 0 && a.TA >= 2 && a.TA <= 8;
-}
-
-// Whether a tile plan runs the ragged paths of 1- and 2-byte units on both sides.
-RR_HD bool ragged_narrow(const TileArgs& a) {
-    return a.unit < 4 && a.g == 1 && a.k == 1 && (a.flags & TF_RAGGED_IN) && (a.flags & TF_RAGGED_OUT);
-}
-
 // ----------------------------------------------------------------- batches
 // Job of workgroup b in a batch group: the largest j with prefix[j] <= b
 // (prefix holds njobs+1 exclusive sums of the jobs' workgroup counts, then the

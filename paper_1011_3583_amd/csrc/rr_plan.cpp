@@ -828,8 +828,25 @@ static bool diag_by_default(const Canon& c) {
     return pow2(c.dims[0] * c.elem_bytes) && pow2(c.dims[1] * c.elem_bytes);
 }
 
-static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const TileOptions& opt,
-                           Plan* p, std::string* why) {
+// Whether a tile of 1- or 2-byte units is better off with G = 1 than with a micro-tile
+// that stores 2 or 4 bytes at a time: its padded rows leave as 16-byte vectors
+// transposed word by word (write_ragged_narrow), its segments are gathered from eight
+// or more LDS banks.  Measured, micro-tile against G = 1: 90 shapes of padded rows of 1
+// to 400 MB 0.95-2.5x, 1.25x in geometric mean (1032 x 1878 of 1 byte 13.1 -> 6.4 us),
+// but 0.82-1.03x for rows of 16, 40 and 56 bytes (32 and 48: 1.2-1.49x); segments 1.08-1.7x where their lanes lie an odd multiple of
+// 32 bytes apart, 0.4-1.27x elsewhere; rows read flat 0.49-0.95x (400000 bytes as rows
+// of 20: 5.5 -> 11.3 us).
+static bool narrow_pays(const TileArgs& a) {
+    if (a.flags & TF_STACK) return false;
+    if (a.flags & TF_IN_SEG) return (16 / a.unit * a.pitch) % 64 != 0;
+    const uint32_t row = a.TA * a.R;
+    return ragged_narrow(a) && (row >= 64 || (row % 16 == 0 && row > 16));
+}
+
+// narrow: micro-tiles of 2- or 4-byte stores are given up for G = 1; *gave_up says
+// whether there was one.
+static rr_status plan_tile_as(uint64_t dst, uint64_t src, const Canon& c, const TileOptions& opt,
+                              bool narrow, bool* gave_up, Plan* p, std::string* why) {
     p->kind = K_TILE;
     TileArgs& a = p->tile;
     std::memset(&a, 0, sizeof(a));
@@ -862,11 +879,10 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
         while (G > 1 && ((d[a1] % G) || (d[b1] % G) || addr_align(src) < U * G ||
                          addr_align(dst) < U * G || (row_starts % (uint64_t)(U * G))))
             G >>= 1;
-        // Micro-tiles that store 2 or 4 bytes at a time lose to G = 1, whose 1- and
-        // 2-byte rows leave as 16-byte vectors transposed word by word
-        // (write_ragged_narrow): 16 shapes each of 3 to 450 MB, 1-byte G = 2 1.42x
-        // and G = 4 1.14x, 2-byte G = 2 1.24x (geometric means).
-        if (opt.max_g == 0 && U * G <= 4 && G > 1 && d[a1] >= 16 && d[b1] >= 16) G = 1;
+        if (narrow && opt.max_g == 0 && U * G <= 4 && G > 1 && d[a1] >= 16 && d[b1] >= 16) {
+            G = 1;
+            *gave_up = true;
+        }
         // Odd extents or pointers rule out aligned micro-tiles: on request keep them
         // anyway with unaligned vector accesses when both fastest extents hold one
         // (the ragged G = 1 paths measured faster on most shapes, so this is a
@@ -1161,8 +1177,7 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
     // batch then has few kernel bodies, whose workgroups overlap better (4096-job
     // call 3450 -> 3257 us, handle 3236 -> 3167 us; uniform 64^3 reversals +4.5 % at
     // 4 and 8 bytes, 512 x 36 transposes -6 % and -2 %).  Wider micro-tiles of 1- and
-    // 2-byte units stay: their G = 1 rows gather byte by byte (1024^2 transposes
-    // -17 %).
+    // 2-byte units that narrow_pays left them stay (1024^2 transposes -17 % as G = 1).
     if (opt.rows_only && !umt && (U >= 4 || G == 2)) G = 1;
     rr_status st = finish_tile(a, U, G, k, ra, flat_ok && !umt, src, b1 > 0 ? (uint64_t)d[b1] : 0,
                                back_to_back() ? (nB == 1 ? a.TB : a.tB[0]) : 0, opt, why);
@@ -1204,6 +1219,14 @@ static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const Til
     p->grid = a.ntiles;
     p->bytes = (uint64_t)c.total_bytes;
     return RR_OK;
+}
+
+static rr_status plan_tile(uint64_t dst, uint64_t src, const Canon& c, const TileOptions& opt,
+                           Plan* p, std::string* why) {
+    bool gave_up = false;
+    const rr_status st = plan_tile_as(dst, src, c, opt, true, &gave_up, p, why);
+    if (!gave_up || (st == RR_OK && narrow_pays(p->tile))) return st;
+    return plan_tile_as(dst, src, c, opt, false, &gave_up, p, why);
 }
 
 // Sets off 16-byte boundaries, or that end inside a vector, take the register

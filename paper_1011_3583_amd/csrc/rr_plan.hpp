@@ -246,6 +246,18 @@ struct TileArgs {
     uint64_t table[RR_MAX_PLANES];
 };
 
+// Whether a tile plan is one for write_split: whole records of 2..8 units read as
+// segments, written through the caches (its kernels hold no other flavour).
+inline bool tile_split(const TileArgs& a) {
+    return (a.flags & TF_IN_SEG) && (a.flags & TF_RAGGED_OUT) && (a.flags & TF_ST_CACHED) && !(a.flags & TF_LD_CACHED) &&
+           a.unit <= 8 && a.k == 1 && a.g == 1 && a.grid_aO < 0 && a.TA >= 2 && a.TA <= 8;
+}
+
+// Whether a tile plan runs the ragged paths of 1- and 2-byte units on both sides.
+inline bool ragged_narrow(const TileArgs& a) {
+    return a.unit < 4 && a.g == 1 && a.k == 1 && (a.flags & TF_RAGGED_IN) && (a.flags & TF_RAGGED_OUT);
+}
+
 // LDS that a single launch of a tile plan asks for.
 inline uint32_t launch_lds(const TileArgs& a) {
     const uint32_t reserve = a.flags & TF_FOUR_PER_CU ? 40960u : a.flags & TF_FIVE_PER_CU ? 32768u : 0u;

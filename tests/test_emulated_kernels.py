@@ -375,6 +375,27 @@ def test_emu_small_crops_keep_whole_records():
         assert int(f["TA"]) == j["dims"][3] and int(f["flags"]) & 8192, (j["dims"], st)
 
 
+# 1- and 2-byte shapes whose extents allow micro-tiles of 2- or 4-byte stores:
+# (dims, perm, element bytes, G of the plan)
+NARROW_CASES = [
+    ((130, 150), (1, 0), 1, 1), ((66, 258), (1, 0), 2, 1), ((18, 20, 150), (2, 1, 0), 1, 1), ((62, 9, 18, 32), (3, 1, 0, 2), 1, 1),   # padded rows
+    ((400, 20), (1, 0), 1, 4), ((800, 28), (1, 0), 1, 4), ((402, 18), (1, 0), 1, 2), ((400, 18), (1, 0), 2, 2), ((130, 62), (1, 0), 1, 2),   # flat
+    ((62, 9, 18, 24), (3, 1, 0, 2), 1, 2), ((62, 9, 18, 28), (3, 1, 0, 2), 1, 2), ((62, 9, 18, 20), (3, 1, 0, 2), 2, 2),   # segments, few banks
+    ((62, 9, 18, 16), (3, 1, 0, 2), 1, 2), ((62, 9, 18, 40), (3, 1, 0, 2), 1, 2), ((62, 9, 18, 56), (3, 1, 0, 2), 1, 2),   # short padded rows
+    ((62, 9, 18, 22), (3, 1, 0, 2), 1, 1), ((62, 9, 18, 30), (3, 1, 0, 2), 1, 1), ((62, 9, 18, 18), (3, 1, 0, 2), 2, 1),   # segments, eight banks
+]
+
+
+def test_emu_narrow_micro_tiles_kept_where_rows_lose():
+    """Micro-tiles of 2- or 4-byte stores become G = 1 rows where the tile has padded
+    rows or segments that spread over the LDS banks, and stay where it is read flat or
+    its segments would not spread.  All match the oracle."""
+    jobs = [_perm_job(d, p, e, 9400 + i) for i, (d, p, e, _) in enumerate(NARROW_CASES)]
+    for j, (_, _, _, g), (st, out) in zip(jobs, NARROW_CASES, emu_runner.run(jobs)):
+        assert st.startswith("ok") and f" g={g} " in st, (j["dims"], g, st)
+        assert np.array_equal(out, oracle.permute(j["input"], j["dims"], j["perm"], j["esize"])), (j["dims"], st)
+
+
 @pytest.mark.parametrize("e", [1, 2, 4])
 def test_emu_segments_only_where_their_banks_spread(e):
     """Rows of whole 16-byte vectors, and rows whose gather would stay on one or two LDS
