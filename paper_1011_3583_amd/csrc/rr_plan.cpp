@@ -787,31 +787,36 @@ static rr_status finish_tile(TileArgs& a, int U, int G, int k, uint64_t row_alig
 
 constexpr int64_t ORDER_IN_NEAR = 48;
 
-// Workgroups per CU.  A CU holds eight tile workgroups; on large problems eight
-// times 256 tiles in flight spread their lines over so many DRAM rows (and, where
-// tiles share lines, over so much L2) that four run faster: asking for 40 KiB of a
-// CU's 160 KiB of LDS holds the launch there.  Measured, eight -> four, us:
-// 16384^2 of 8 bytes 800 -> 785, 512 x 512 x 256 under (2,1,0) of 4 bytes 101.5 ->
-// 98.6, under (1,2,0) of 16 bytes 353 -> 339; sharing lines: 8193 x 8195 of 4 bytes
-// 139 -> 128, of 16 bytes 468 -> 433, 209 x 1169374 of 1 byte 185 -> 120.  Left at
-// eight: tiles well under 16 KiB or with short rows, whose latency needs the waves
-// (23-element rows of 4 bytes 164 -> 208); tiles that hold a side whole, which read
-// or write one long run (509 x 29 x 3388 of 8 bytes 153 -> 173); grids of few tiles
-// per CU, whose last wave would be emptier (28 MiB: 17.1 -> 18.3; 9184 tiles that share no
-// lines, 240 x 36736 of 16 bytes, 52.3 -> 53.2, while 16384 gain above); aligned tiles of
-// 2 bytes, and of 4 bytes in diagonal order (0 to -4 %).  Odd 2-byte tiles of 8
-// to 14 KiB stay between, at five (6 x 36 x 236 x 629 x 13 under (3,0,1,4,2): 485 us
-// at eight, 426 at five; 227 x 112 x 631 x 23 under (3,1,2,0): 418 and 454).
-static uint32_t tile_reserve(const TileArgs& a, const TileOptions& opt) {
-    if (opt.rows_only || a.ntiles < 8192 || (a.flags & TF_STACK)) return 0;
+// Workgroups per CU.  A CU holds eight tile workgroups, and eight times 256 tiles in
+// flight touch twice the 4 MB L2 of each XCD: the two parts of a line that tiles share
+// then meet in HBM instead.  On large grids four run faster; asking for 40 KiB of a
+// CU's 160 KiB of LDS holds the launch there.  Measured, eight against four, on 900
+// random shapes of 120 MB to 2 GB (tiles of 14 KiB and more with whole lines on both
+// sides, neither side held whole; geometric mean and range of the gain):
+//   sharing lines: 1-byte units from 12288 tiles 1.10x (0.94 to 1.51), 2-byte 1.10x
+//     (0.99 to 1.41); both 0.80 to 1.25x below.  16-byte ones from 16384 tiles 1.03x
+//     (0.98 to 1.12), 0.91 to 1.04x below.  4-byte ones from 16384 tiles in two-axis
+//     problems or with micro-tiles 1.04x (0.98 to 1.15), 0.84 to 1.1x otherwise.
+//     Elements of several units 0.88 to 1.0x: left at eight;
+//   8-byte units from 65536 tiles, sharing lines 1.035x (0.94 to 1.15) or not 1.02x
+//     (0.98 to 1.09) up to three axes; below that 0.88 to 1.05x;
+//   16-byte units that share no lines, up to three axes, from 32768 tiles: 1.03x (0.975
+//     to 1.125); other units that share none 0.88 to 1.03x.
+// Tiles under 14 KiB or with short rows need the waves to hide latency (23-element
+// rows of 4 bytes 164 -> 208 us; 2-byte ones at five per CU 0.74 to 1.1x).
+static uint32_t tile_reserve(const TileArgs& a, int rank, const TileOptions& opt) {
+    if (opt.rows_only || a.k != 1 || (a.flags & TF_STACK) || a.grid_aO < 0 || a.grid_bO < 0) return 0;
+    if (a.lds_bytes < 14336 || a.TA * a.R < 128 || a.TB * a.R < 128) return 0;
     const bool share = (a.flags & TF_XCD) != 0;
-    const bool full = a.lds_bytes >= 14336 && (uint64_t)a.TA * a.R >= 128 && (uint64_t)a.TB * a.R >= 128;
-    if (!full)
-        return share && a.unit == 2 && a.lds_bytes >= 8192 && (a.flags & TF_RAGGED_IN) && (a.flags & TF_RAGGED_OUT) ? TF_FIVE_PER_CU : 0;
-    if (a.grid_aO < 0 || a.grid_bO < 0) return 0;
-    if (!share && a.ntiles < 16384) return 0;
-    if (!share && (a.unit == 2 || (a.unit == 4 && (a.flags & TF_DIAG)))) return 0;
-    return TF_FOUR_PER_CU;
+    uint32_t from = 16384;
+    bool ok = share;
+    switch (a.unit) {
+        case 1: case 2: from = 12288; break;
+        case 4: ok = share && (a.g > 1 || rank == 2); break;
+        case 8: from = 65536; ok = share || rank <= 3; break;
+        default: from = share ? 16384 : 32768; ok = share || rank <= 3; break;
+    }
+    return ok && a.ntiles >= from ? TF_FOUR_PER_CU : 0;
 }
 
 // Built-in diagonal tile order: 2-D transposes of 1-8-byte elements whose rows
@@ -1215,7 +1220,7 @@ static rr_status plan_tile_as(uint64_t dst, uint64_t src, const Canon& c, const 
     }
     if (a.ngrid >= 2 && (opt.diag == 1 || (opt.diag == -1 && diag_by_default(c)))) a.flags |= TF_DIAG;
     if (order_out) a.flags |= TF_ORDER_OUT;
-    a.flags |= tile_reserve(a, opt);
+    a.flags |= tile_reserve(a, r, opt);
     p->grid = a.ntiles;
     p->bytes = (uint64_t)c.total_bytes;
     return RR_OK;

@@ -185,7 +185,7 @@ enum TileFlags : uint32_t {
                             // LDS rows unpadded within a segment
     TF_ORDER_OUT = 16384u,  // the tile grid is walked in output order (planning only)
     TF_FOUR_PER_CU = 32768u,// a single launch reserves LDS so that at most four of its
-    TF_FIVE_PER_CU = 65536u,// (at most five) workgroups share a CU
+                            // workgroups share a CU
 };
 
 struct TileArgs {
@@ -260,7 +260,7 @@ inline bool ragged_narrow(const TileArgs& a) {
 
 // LDS that a single launch of a tile plan asks for.
 inline uint32_t launch_lds(const TileArgs& a) {
-    const uint32_t reserve = a.flags & TF_FOUR_PER_CU ? 40960u : a.flags & TF_FIVE_PER_CU ? 32768u : 0u;
+    const uint32_t reserve = a.flags & TF_FOUR_PER_CU ? 40960u : 0u;
     return a.lds_bytes > reserve ? a.lds_bytes : reserve;
 }
 

@@ -574,3 +574,24 @@ def test_requested_tile_size_holds_for_small_crops():
             assert kib * 512 < lds <= kib * 1024, (kib, lds)
     finally:
         rr.set_tile_override()
+
+
+# (dims, perm, element bytes, whether the launch holds four workgroups per CU)
+RESERVE_CASES = [
+    ((8193, 8195), (1, 0), 4, True), ((4096, 4099), (1, 0), 4, False),         # shared lines, two axes; a small grid
+    ((345, 292614), (1, 0), 2, True), ((18, 14, 1016, 266), (0, 3, 2, 1), 2, False),
+    ((45, 497, 3467), (0, 2, 1), 4, False), ((784, 624, 576), (0, 2, 1), 1, True),
+    ((1812, 222, 47, 18), (1, 2, 0, 3), 1, False),                             # elements of several units
+    ((33, 236, 122, 92), (3, 1, 0, 2), 2, False),                              # 2-byte tiles under 14 KiB
+    ((5296, 8608), (1, 0), 8, False), ((16384, 16384), (1, 0), 8, True),       # 8-byte units: by the grid
+    ((512, 512, 256), (2, 1, 0), 4, False), ((8192, 8192), (1, 0), 4, False),  # no shared lines
+    ((8192, 8192), (1, 0), 16, True), ((4096, 4096), (1, 0), 16, False), ((64, 64, 64, 64, 8), (4, 3, 2, 1, 0), 16, False),
+]
+
+
+@pytest.mark.parametrize("dims,perm,e,four", RESERVE_CASES)
+def test_four_workgroups_per_cu_by_grid_and_unit(dims, perm, e, four):
+    """Which single tile launches reserve LDS for four workgroups per CU (flag 32768);
+    nothing reserves for any other number (65536)."""
+    flags = int(rr.plan_describe(dims, perm, e, 1 << 40, 1 << 42)["flags"])
+    assert bool(flags & 32768) == four and not flags & 65536, flags
