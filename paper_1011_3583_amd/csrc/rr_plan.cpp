@@ -785,8 +785,6 @@ static rr_status finish_tile(TileArgs& a, int U, int G, int k, uint64_t row_alig
     return RR_OK;
 }
 
-constexpr int64_t ORDER_IN_NEAR = 48;
-
 // Workgroups per CU.  A CU holds eight tile workgroups, and eight times 256 tiles in
 // flight touch twice the 4 MB L2 of each XCD: the two parts of a line that tiles share
 // then meet in HBM instead.  On large grids four run faster; asking for 40 KiB of a
@@ -831,6 +829,69 @@ static bool diag_by_default(const Canon& c) {
     if (c.rank != 2 || c.perm[0] != 1 || c.strided || c.elem_bytes > 8 || c.total_bytes < (16ll << 20)) return false;
     auto pow2 = [](int64_t x) { return x >= 4096 && (x & (x - 1)) == 0; };
     return pow2(c.dims[0] * c.elem_bytes) && pow2(c.dims[1] * c.elem_bytes);
+}
+
+// What walking the tile grid in input (or output) order costs in lines that two tiles
+// share, in lines per line of the tile: for each side, the ends of a tile's rows that
+// lie inside a 128-byte line, each weighted by how likely the line has left L2 when the
+// neighbour comes.  The neighbour is the next tile along the row's outer axis, or past
+// its end the next one along the slower axes; where those are in the tile, the end is
+// shared with the tile itself but for its last row.  d tiles apart, a line is gone with
+// d^2 / (d^2 + near^2); a line written in two parts counts `twice` times one read
+// twice.  Both numbers are fitted, on 3000 random shapes of 4 MB to 1 GB, 1- to 16-byte
+// elements, timed in both orders: 64 tiles (128 for 1- and 2-byte units of three axes
+// and more), 1.5 for 1- and 2-byte units and 3 for wider ones, whose rows are longer.
+// Going by this cost where the orders differ by WALK_MARGIN and by element size
+// elsewhere ran 1.044x as fast in geometric mean as element size alone (up to 2.15x);
+// 14 of the shapes ran more than 2.5 % slower (0.70x at worst).  The distance along
+// the fastest axis alone, which the order went by before, left 115 of them.
+constexpr double WALK_MARGIN = 0.1;
+static double walk_cost(const Canon& c, int U, const int* pm, const bool* inA, const bool* inB, const int64_t* t,
+                        const int64_t* n, uint64_t src, uint64_t dst, bool by_out) {
+    const double near = U <= 2 && c.rank > 2 ? 128.0 : 64.0, twice = U <= 2 ? 1.5 : 3.0;
+    const int r = c.rank;
+    int64_t stride[MAXR];   // tiles from one along an axis to the next
+    int64_t acc = 1;
+    for (int oi = r - 1; oi >= 0; --oi) {
+        const int s = by_out ? pm[oi] : oi;
+        stride[s] = acc;
+        acc *= n[s];
+    }
+    auto gone = [&](int64_t d) {
+        const double q = (double)d * (double)d;
+        return q / (q + near * near);
+    };
+    double total = 0;
+    for (int side = 0; side < 2; ++side) {
+        const bool* own = side ? inB : inA;
+        auto axis = [&](int j) { return side ? pm[j] : j; };
+        int j = r - 1, outer = axis(j);
+        int64_t row = c.elem_bytes, block = c.elem_bytes;   // bytes of a tile's row, of its axes whole
+        for (; j >= 0 && own[axis(j)]; --j) {
+            outer = axis(j);
+            row *= t[outer];
+            block *= c.dims[outer];
+        }
+        const bool split_at_block = ((side ? dst : src) | (uint64_t)block) % 128 != 0;
+        const bool split_inside = split_at_block || row % 128 != 0;
+        double lines = 0;
+        if (n[outer] > 1 && split_inside) lines += (double)(n[outer] - 1) / (double)n[outer] * gone(stride[outer]);
+        double ends = split_at_block ? 1.0 / (double)n[outer] : 0.0;
+        int64_t back = (n[outer] - 1) * stride[outer];
+        for (; j >= 0 && ends > 0; --j) {
+            const int s = axis(j);
+            if (!side && c.sinb[s] != block) break;   // a box: the next row starts elsewhere
+            block *= c.dims[s];
+            ends /= (double)t[s];
+            if (n[s] > 1) {
+                lines += ends * (double)(n[s] - 1) / (double)n[s] * gone(stride[s] - back);
+                back += (n[s] - 1) * stride[s];
+                ends /= (double)n[s];
+            }
+        }
+        total += (side ? twice : 1.0) * std::min(4.0, lines * 128.0 / (double)std::max<int64_t>(row, 32));
+    }
+    return total;
 }
 
 // Whether a tile of 1- or 2-byte units is better off with G = 1 than with a micro-tile
@@ -1189,33 +1250,14 @@ static rr_status plan_tile_as(uint64_t dst, uint64_t src, const Canon& c, const 
     if (st != RR_OK) return st;
     cache_policy(a, opt);
     // Tiles that share lines: the walk decides how far apart the tiles are that touch
-    // the two parts of a line.  Output order puts tiles that share output lines side
-    // by side, and those that share input lines as far apart as there are tiles
-    // along the axes between (far_out); input order the other way round (far_in).
-    // A line written in two parts costs more than one read twice, unless its second
-    // part comes while the first is still in L2: input order where far_in is the
-    // nearer and at most ORDER_IN_NEAR tiles, else output order.  Measured on 150
-    // shapes of 4 MB to 1 GB, 1-16-byte elements: input order up to 1.25x faster below that
-    // line (256013 x 1043 of 2 bytes, far_in 9), output order up to 2.1x above it
-    // (9744 x 18176 of 2 bytes, 142: 1.5x; 107 x 3135674: 1.85x).
+    // the two parts of a line, and so whether its second part finds it in L2.
     if (opt.order_out < 0 && (a.flags & TF_XCD)) {
-        auto distance = [&](bool by_out, bool out_side) {
-            // the fastest axis, on that side, along which there are several tiles
-            int x = -1;
-            for (int j = r - 1; j >= 0 && x < 0; --j) {
-                const int s = out_side ? pm[j] : j;
-                if (tiles_along(s) > 1) x = s;
-            }
-            int64_t dist = 1;
-            for (int oi = r - 1; oi >= 0; --oi) {
-                const int s = by_out ? pm[oi] : oi;
-                if (s == x) break;
-                dist *= tiles_along(s);
-            }
-            return dist;
-        };
-        const int64_t far_in = distance(false, true), far_out = distance(true, false);
-        order_out = !(far_in < far_out && far_in <= ORDER_IN_NEAR);
+        int64_t n[MAXR];
+        for (int s = 0; s < r; ++s) n[s] = tiles_along(s);
+        const double in_first = walk_cost(c, U, pm, inA, inB, t, n, src, dst, false);
+        const double out_first = walk_cost(c, U, pm, inA, inB, t, n, src, dst, true);
+        const double gain = in_first - out_first;
+        if (gain > WALK_MARGIN || gain < -WALK_MARGIN) order_out = gain > 0;
         build_grid(order_out);
     }
     if (a.ngrid >= 2 && (opt.diag == 1 || (opt.diag == -1 && diag_by_default(c)))) a.flags |= TF_DIAG;

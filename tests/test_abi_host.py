@@ -595,3 +595,27 @@ def test_four_workgroups_per_cu_by_grid_and_unit(dims, perm, e, four):
     nothing reserves for any other number (65536)."""
     flags = int(rr.plan_describe(dims, perm, e, 1 << 40, 1 << 42)["flags"])
     assert bool(flags & 32768) == four and not flags & 65536, flags
+
+
+# (dims, perm, element bytes, tile order): the order measured faster on shapes whose tiles
+# share lines
+ORDER_CASES = [
+    ((468, 166, 5656), (0, 2, 1), 1, "in"), ((96, 144, 6, 48, 80), (2, 4, 3, 0, 1), 2, "in"),
+    ((45, 14, 46, 1312), (1, 3, 0, 2), 16, "out"), ((27, 645, 52, 60), (1, 3, 0, 2), 16, "out"),
+    ((21, 95, 150, 252), (1, 3, 0, 2), 4, "out"), ((102, 5005, 480), (0, 2, 1), 4, "out"),   # rows that end on lines on one side
+    ((156, 2748618), (1, 0), 2, "out"), ((2995, 259995), (1, 0), 1, "out"), ((9744, 18176), (1, 0), 2, "out"),
+    ((209, 1169374), (1, 0), 1, "out"), ((256013, 1043), (1, 0), 2, "in"), ((863824, 130), (1, 0), 4, "in"),
+]
+
+
+@pytest.mark.parametrize("dims,perm,e,order", ORDER_CASES)
+def test_tile_order_follows_the_shared_lines(dims, perm, e, order):
+    """The built-in walk of tiles that share 128-byte lines, and both walks on request."""
+    args = (dims, perm, e, 1 << 40, 1 << 42)
+    try:
+        assert rr.plan_describe(*args)["order"] == order
+        for out in (True, False):
+            rr.set_tile_override(order_out=out)
+            assert rr.plan_describe(*args)["order"] == ("out" if out else "in")
+    finally:
+        rr.set_tile_override()
