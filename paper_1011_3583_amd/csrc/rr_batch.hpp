@@ -106,8 +106,9 @@ rr_status plan_batch(const rr_job* jobs, int njobs, const TileOptions& opt, Batc
 // jobs, without planning them: what plan_batch reports, before any planning.
 rr_status validate_batch(const rr_job* jobs, int njobs, std::string* why, int* bad_job);
 
-// Validate one job and plan it (no overlap check against other jobs).
-rr_status plan_job(const rr_job& j, const TileOptions& opt, Plan* p, std::string* why);
+// Validate one job and plan it (no overlap check against other jobs); rows: with the
+// G = 1 rows of batch_job_options.
+rr_status plan_job(const rr_job& j, const TileOptions& opt, Plan* p, std::string* why, bool rows = true);
 
 // Group already planned entries into a batch table.
 rr_status build_batch(const std::vector<BatchEntry>& entries, BatchPlan* out, std::string* why);

@@ -3,6 +3,7 @@
 #include <unistd.h>
 
 #include <algorithm>
+#include <atomic>
 #include <condition_variable>
 #include <cstring>
 #include <exception>
@@ -54,11 +55,20 @@ static rr_status validate_job(const rr_job& j, Canon* c, std::string* why) {
     return RR_OK;
 }
 
-rr_status plan_job(const rr_job& j, const TileOptions& opt, Plan* p, std::string* why) {
+rr_status plan_job(const rr_job& j, const TileOptions& opt, Plan* p, std::string* why, bool rows) {
     Canon c;
     rr_status st = validate_job(j, &c, why);
     if (st != RR_OK) return st;
-    return plan_permute((uint64_t)j.dst, (uint64_t)j.src, c, batch_job_options(opt, c.total_bytes), p, why);
+    TileOptions o = batch_job_options(opt, c.total_bytes);
+    if (!rows) o.rows_only = 0;
+    return plan_permute((uint64_t)j.dst, (uint64_t)j.src, c, o, p, why);
+}
+
+// The kernel body a plan runs in a batch: tile (unit and G), run or copy (vector width).
+static int body_variant(const Plan& p) {
+    if (p.kind == K_COPY) return (int)p.copy.wbytes;
+    if (p.kind == K_RUN) return (int)p.run.wbytes;
+    return (int)(p.tile.unit * 100 + p.tile.g);
 }
 
 // Host threads that plan (or validate) a batch of njobs: one below 256 jobs,
@@ -181,6 +191,15 @@ static void run_slices(int nt, Body body) {
     for (std::thread& x : th) x.join();
 }
 
+// A batch whose jobs all run one kernel body has none to save by planning them as G = 1
+// rows, and up to this many bytes per side, where it runs from the Infinity Cache, it
+// is faster with its micro-tiles.  MI355X, handles, micro-tiles / rows, us: 512 x 36
+// transposes of 4 bytes 38 MB 15.3 / 18.6, 442 MB 178 / 185, 737 MB 309 / 297; 1024^2 of
+// 4 bytes 268 MB 95 / 103, 537 MB 185 / 189, 755 MB 265 / 258, 1.7 GB 596 / 558; 64^3
+// reversals of 4 bytes 134 MB 51 / 55, 403 MB 145 / 146, 671 MB 242 / 230; 1000 x 72
+// of 8 bytes 173 MB 72 / 73, 576 MB 243 / 209.
+constexpr uint64_t ALIKE_MAX_BYTES = 512ull << 20;
+
 rr_status plan_batch(const rr_job* jobs, int njobs, const TileOptions& opt, BatchPlan* out,
                      std::string* why, int* bad_job) {
     *bad_job = -1;
@@ -211,14 +230,48 @@ rr_status plan_batch(const rr_job* jobs, int njobs, const TileOptions& opt, Batc
     std::vector<int> bad((size_t)nt, -1);
     std::vector<rr_status> sts((size_t)nt, RR_OK);
     std::vector<std::string> whys((size_t)nt);
+    // Jobs keep their micro-tiles until the batch turns out to run several kernel
+    // bodies or to exceed ALIKE_MAX_BYTES; from then on they are planned as rows, and
+    // those planned before are planned again.  Either holds of a batch whichever
+    // thread finds it first, so the plan does not depend on the threads.
+    const bool choose = !override_active(opt);
+    std::atomic<bool> rows{!choose};
+    std::atomic<int> body{-1};
+    std::atomic<uint64_t> bytes{0};
     auto slice = [&](int t) {
         const int lo = (int)((int64_t)njobs * t / nt), hi = (int)((int64_t)njobs * (t + 1) / nt);
         for (int i = lo; i < hi; ++i) {
-            const rr_status st = plan_job(jobs[i], opt, &plans[i], &whys[(size_t)t]);
+            const bool as_rows = rows.load(std::memory_order_relaxed);
+            const rr_status st = plan_job(jobs[i], opt, &plans[i], &whys[(size_t)t], as_rows);
             if (st != RR_OK) { sts[(size_t)t] = st; bad[(size_t)t] = i; return; }
+            if (as_rows || plans[i].kind == K_EMPTY) continue;
+            const int b = (int)plans[i].kind * 10000 + body_variant(plans[i]);
+            int first = -1;
+            if ((!body.compare_exchange_strong(first, b) && first != b) ||
+                bytes.fetch_add(plans[i].bytes) + plans[i].bytes > ALIKE_MAX_BYTES)
+                rows.store(true, std::memory_order_relaxed);
         }
     };
     run_slices(nt, slice);
+    auto micro = [&](int i) {   // a micro-tile that rows would replace
+        const TileArgs& a = plans[i].tile;
+        return plans[i].kind == K_TILE && a.g > 1 && (a.unit >= 4 || a.g == 2);
+    };
+    auto again = [&](int t) {
+        const int lo = (int)((int64_t)njobs * t / nt), hi = (int)((int64_t)njobs * (t + 1) / nt);
+        for (int i = lo; i < hi && sts[(size_t)t] == RR_OK; ++i) {
+            if (!micro(i)) continue;
+            sts[(size_t)t] = plan_job(jobs[i], opt, &plans[i], &whys[(size_t)t]);
+            if (sts[(size_t)t] != RR_OK) bad[(size_t)t] = i;
+        }
+    };
+    if (choose && rows.load() && std::all_of(sts.begin(), sts.end(), [](rr_status st) { return st == RR_OK; })) {
+        int left = 0;
+        for (int i = 0; i < njobs; ++i) left += micro(i);
+        if (left > 128) run_slices(nt, again);
+        else if (left)
+            for (int t = 0; t < nt; ++t) again(t);
+    }
     for (int t = 0; t < nt; ++t)
         if (sts[(size_t)t] != RR_OK) { *why = whys[(size_t)t]; *bad_job = bad[(size_t)t]; return sts[(size_t)t]; }
     std::vector<Interval> dsts, srcs;
@@ -304,10 +357,7 @@ rr_status build_batch(const std::vector<BatchEntry>& entries, BatchPlan* out, st
             *why = "batch entry of a kind the batched kernels do not run";
             return RR_ERR_UNSUPPORTED;
         }
-        int variant = 0;
-        if (p.kind == K_COPY) variant = (int)p.copy.wbytes;
-        else if (p.kind == K_RUN) variant = (int)p.run.wbytes;
-        else variant = (int)(p.tile.unit * 100 + p.tile.g);
+        const int variant = body_variant(p);
         int lds_class = 0;
         if (p.kind == K_TILE) lds_class = p.tile.lds_bytes <= 16384 ? 0 : p.tile.lds_bytes <= 32768 ? 1 : 2;
         fam[Key{(int)p.kind, variant, lds_class}].push_back(i);

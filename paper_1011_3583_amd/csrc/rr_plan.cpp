@@ -56,6 +56,7 @@ TileOptions batch_job_options(const TileOptions& opt, int64_t bytes_per_side) {
         o.out_row_bytes = 256;
         o.order_out = 1;
         o.cache = 3;
+        o.batched = 1;
         o.rows_only = 1;
     }
     return o;
@@ -677,7 +678,7 @@ static void cache_policy(TileArgs& a, const TileOptions& opt) {
     if (pol < 0) pol = split && !table ? 2 : 0;
     // batched tiles of 16-byte units that share no line gain nothing from the caches
     // (1024^2 transposes 4600 -> 6220 GB/s streamed, 64^3 reversals 4770 -> 6150)
-    if (opt.rows_only && a.unit == 16 && !split) pol = 0;
+    if (opt.batched && a.unit == 16 && !split) pol = 0;
     if (pol & 1) a.flags |= TF_LD_CACHED;
     if (pol & 2) a.flags |= TF_ST_CACHED;
     const bool xcd = opt.xcd >= 0 ? opt.xcd > 0 : split && pol != 0 && !table;
@@ -803,7 +804,7 @@ static rr_status finish_tile(TileArgs& a, int U, int G, int k, uint64_t row_alig
 // Tiles under 14 KiB or with short rows need the waves to hide latency (23-element
 // rows of 4 bytes 164 -> 208 us; 2-byte ones at five per CU 0.74 to 1.1x).
 static uint32_t tile_reserve(const TileArgs& a, int rank, const TileOptions& opt) {
-    if (opt.rows_only || a.k != 1 || (a.flags & TF_STACK) || a.grid_aO < 0 || a.grid_bO < 0) return 0;
+    if (opt.batched || a.k != 1 || (a.flags & TF_STACK) || a.grid_aO < 0 || a.grid_bO < 0) return 0;
     if (a.lds_bytes < 14336 || a.TA * a.R < 128 || a.TB * a.R < 128) return 0;
     const bool share = (a.flags & TF_XCD) != 0;
     uint32_t from = 16384;
@@ -1241,9 +1242,9 @@ static rr_status plan_tile_as(uint64_t dst, uint64_t src, const Canon& c, const 
     // Batched jobs of 4-16-byte units write G = 1 rows (one gathered 16-byte vector
     // per lane at any alignment), and so do 1- and 2-byte ones left with G = 2: a
     // batch then has few kernel bodies, whose workgroups overlap better (4096-job
-    // call 3450 -> 3257 us, handle 3236 -> 3167 us; uniform 64^3 reversals +4.5 % at
-    // 4 and 8 bytes, 512 x 36 transposes -6 % and -2 %).  Wider micro-tiles of 1- and
-    // 2-byte units that narrow_pays left them stay (1024^2 transposes -17 % as G = 1).
+    // call 3450 -> 3257 us, handle 3236 -> 3167 us); plan_batch says which batches.
+    // Wider micro-tiles of 1- and 2-byte units that narrow_pays left them stay (1024^2
+    // transposes -17 % as G = 1).
     if (opt.rows_only && !umt && (U >= 4 || G == 2)) G = 1;
     rr_status st = finish_tile(a, U, G, k, ra, flat_ok && !umt, src, b1 > 0 ? (uint64_t)d[b1] : 0,
                                back_to_back() ? (nB == 1 ? a.TB : a.tB[0]) : 0, opt, why);

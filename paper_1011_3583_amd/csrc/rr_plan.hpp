@@ -281,6 +281,7 @@ struct TileOptions {
                             // of the G = 1 ragged paths), 2 everywhere (testing)
     int fill = -1;          // refit odd extents for fewer, fuller tiles: 1 on, 0 off, -1 built-in
     int weave = 1;          // interlace of 2-4 aligned sets of 1-8-byte elements in registers (0: LDS tile)
+    int batched = 0;        // a small job of a batch (batch_job_options)
     int rows_only = 0;      // G = 1 once the extents are chosen, where it is as good (batched jobs)
     int max_lds = 65536;    // hard limit
     bool use_tuned = false; // a tuned shape cached for the problem replaces these options
@@ -302,7 +303,8 @@ bool override_active(const TileOptions& o);
 // runs and tiles.  Unless opt is an override (or a tuner candidate), a job of at
 // most BATCH_SMALL_JOB_BYTES per side gets 512-byte input and 256-byte output
 // row targets, output-order tile traversal, cached tile accesses (but see
-// cache_policy for 16-byte units) and G = 1 rows for 4-16-byte units.  That is
+// cache_policy for 16-byte units) and G = 1 rows for 4-16-byte units (a batch of one
+// kernel body goes without the rows: plan_batch).  That is
 // the shape the batch tuner picks for many small odd-shaped jobs, whose
 // neighbours in a group share lines and run from L2.
 constexpr int64_t BATCH_SMALL_JOB_BYTES = 128ll << 20;

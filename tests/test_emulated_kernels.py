@@ -755,6 +755,25 @@ def test_emu_fused_launch_covers_each_workgroup_once(max_g, outside):
             (j["dims"], j["perm"], j["esize"])
 
 
+@pytest.mark.parametrize("dims,perm,e,njobs,own,rows", [
+    ((512, 36), (1, 0), 4, 5, 404, 401), ((24, 20, 16), (2, 1, 0), 8, 5, 802, 801), ((100, 62), (1, 0), 4, 5, 402, 401),
+    ((160, 80), (1, 0), 1, 5, 108, 108), ((12, 16), (1, 0), 16, 5, 1601, 1601), ((32, 16), (1, 0), 4, 600, 404, 401)])
+def test_emu_batches_of_one_body_keep_its_micro_tiles(dims, perm, e, njobs, own, rows):
+    """A batch whose jobs all run one kernel body keeps that body's micro-tiles; one job
+    of another body, first or last (and on another planning thread), plans all of them
+    as rows.  All match the oracle."""
+    few = [_perm_job(dims, perm, e, 14000 + i) for i in range(3)]
+    alike = [few[i % 3] for i in range(njobs)]
+    other = _perm_job((50, 8), (0, 1), 2, 14100)
+    for jobs, want in ((alike, own), ([other] + alike, rows), (alike + [other], rows)):
+        status, outs = emu_runner.run([dict(op="batched", jobs=jobs)])[0]
+        assert status.startswith("ok"), status
+        bodies = {tuple(map(int, v.split(":"))) for v in status.split("variants=")[1].split()[0].split(",")}
+        assert {v for _, v in bodies if v >= 100} == {want}, (len(jobs), status)
+        for j, out in zip(jobs, outs):
+            assert np.array_equal(out, oracle.permute(j["input"], j["dims"], j["perm"], j["esize"])), j["dims"]
+
+
 @pytest.mark.parametrize("chunk", [1, 3])
 def test_emu_chunked_entries(chunk):
     """Jobs cut into ranges of their own workgroups, ranges of different jobs

@@ -327,3 +327,24 @@ def test_fused_launch_matches_the_groups_one_by_one(rr, max_g):
             b.close()
     finally:
         rr.set_tile_override(0, 0, None)
+
+
+@pytest.mark.parametrize("dims,perm,e", [((512, 36), (1, 0), 4), ((64, 48, 40), (2, 1, 0), 8), ((1000, 20), (1, 0), 1),
+                                         ((100, 62), (1, 0), 4), ((400, 18), (1, 0), 2)])
+def test_batches_of_one_body(rr, dims, perm, e):
+    """Jobs of one shape keep their micro-tiles in a batch; with one job of another shape
+    they go as rows.  Handle and one-shot call, bit-exact."""
+    for extra in ([], [{"dims": (33, 50), "perm": (1, 0), "esize": 2}]):
+        specs = [{"dims": dims, "perm": perm, "esize": e}] * 6 + extra
+        _say("one body", dims, e, len(specs))
+        J = Jobs(rr, specs, 71)
+        st = torch.cuda.current_stream()
+        b = rr.Batch(J.arr, 0)
+        b.launch(st)
+        torch.cuda.synchronize()
+        _check_all_vs_oracle(J)
+        J.dst.zero_()
+        rr.check(rr.permute_batched_raw(J.arr, len(specs), st.cuda_stream))
+        torch.cuda.synchronize()
+        _check_all_vs_oracle(J)
+        b.close()
