@@ -232,44 +232,46 @@ rr_status plan_batch(const rr_job* jobs, int njobs, const TileOptions& opt, Batc
     std::vector<std::string> whys((size_t)nt);
     // Jobs keep their micro-tiles until the batch turns out to run several kernel
     // bodies or to exceed ALIKE_MAX_BYTES; from then on they are planned as rows, and
-    // those planned before are planned again.  Either holds of a batch whichever
-    // thread finds it first, so the plan does not depend on the threads.
+    // those planned before (the first of each slice) are planned again.  Either holds
+    // of a batch whichever thread finds it first, so the plan does not depend on the
+    // threads.
     const bool choose = !override_active(opt);
     std::atomic<bool> rows{!choose};
     std::atomic<int> body{-1};
     std::atomic<uint64_t> bytes{0};
+    auto lo_of = [&](int t) { return (int)((int64_t)njobs * t / nt); };
+    std::vector<int> micro_end((size_t)nt);   // a slice's jobs before this one kept micro-tiles
     auto slice = [&](int t) {
-        const int lo = (int)((int64_t)njobs * t / nt), hi = (int)((int64_t)njobs * (t + 1) / nt);
-        for (int i = lo; i < hi; ++i) {
+        int kept = lo_of(t);
+        for (int i = kept; i < lo_of(t + 1); ++i) {
             const bool as_rows = rows.load(std::memory_order_relaxed);
             const rr_status st = plan_job(jobs[i], opt, &plans[i], &whys[(size_t)t], as_rows);
             if (st != RR_OK) { sts[(size_t)t] = st; bad[(size_t)t] = i; return; }
-            if (as_rows || plans[i].kind == K_EMPTY) continue;
+            if (as_rows) continue;
+            kept = i + 1;
+            if (plans[i].kind == K_EMPTY) continue;
             const int b = (int)plans[i].kind * 10000 + body_variant(plans[i]);
             int first = -1;
             if ((!body.compare_exchange_strong(first, b) && first != b) ||
                 bytes.fetch_add(plans[i].bytes) + plans[i].bytes > ALIKE_MAX_BYTES)
                 rows.store(true, std::memory_order_relaxed);
         }
+        micro_end[(size_t)t] = kept;
     };
     run_slices(nt, slice);
-    auto micro = [&](int i) {   // a micro-tile that rows would replace
-        const TileArgs& a = plans[i].tile;
-        return plans[i].kind == K_TILE && a.g > 1 && (a.unit >= 4 || a.g == 2);
-    };
     auto again = [&](int t) {
-        const int lo = (int)((int64_t)njobs * t / nt), hi = (int)((int64_t)njobs * (t + 1) / nt);
-        for (int i = lo; i < hi && sts[(size_t)t] == RR_OK; ++i) {
-            if (!micro(i)) continue;
-            sts[(size_t)t] = plan_job(jobs[i], opt, &plans[i], &whys[(size_t)t]);
-            if (sts[(size_t)t] != RR_OK) bad[(size_t)t] = i;
+        for (int i = lo_of(t); i < micro_end[(size_t)t]; ++i) {
+            const TileArgs& a = plans[i].tile;
+            if (plans[i].kind != K_TILE || a.g == 1 || (a.unit < 4 && a.g != 2)) continue;   // rows already, or kept
+            const rr_status st = plan_job(jobs[i], opt, &plans[i], &whys[(size_t)t]);
+            if (st != RR_OK) { sts[(size_t)t] = st; bad[(size_t)t] = i; return; }
         }
     };
     if (choose && rows.load() && std::all_of(sts.begin(), sts.end(), [](rr_status st) { return st == RR_OK; })) {
         int left = 0;
-        for (int i = 0; i < njobs; ++i) left += micro(i);
+        for (int t = 0; t < nt; ++t) left += micro_end[(size_t)t] - lo_of(t);
         if (left > 128) run_slices(nt, again);
-        else if (left)
+        else
             for (int t = 0; t < nt; ++t) again(t);
     }
     for (int t = 0; t < nt; ++t)
