@@ -348,3 +348,20 @@ def test_batches_of_one_body(rr, dims, perm, e):
         torch.cuda.synchronize()
         _check_all_vs_oracle(J)
         b.close()
+
+
+@pytest.mark.parametrize("njobs", [1, 4, 21, 22, 23, 60])
+def test_one_shot_table_upload_both_ways(rr, njobs):
+    """Job tables below and above 16 KiB (21 and 22 tile jobs) go up by different means:
+    calls with other jobs in the same staging slots, back to back, are bit-exact."""
+    st = torch.cuda.current_stream()
+    sets = []
+    for k in range(5):   # more than the staging slots
+        specs = [{"dims": (24 + k, 17 + i), "perm": (1, 0), "esize": 4} for i in range(njobs)]
+        sets.append(Jobs(rr, specs, 80 + k))
+    _say("table upload", njobs)
+    for J in sets:
+        rr.check(rr.permute_batched_raw(J.arr, njobs, st.cuda_stream))
+    torch.cuda.synchronize()
+    for J in sets:
+        _check_all_vs_oracle(J)
