@@ -157,6 +157,7 @@ struct Launches {
     std::vector<const BatchGroup*> single;
     uint64_t fused_cost = 0;
 
+    Launches() { fused.ngroups = 0; }
     Launches(const BatchPlan& p, const uint8_t* dev_table, GroupLaunch how) {
         std::vector<uint8_t> in(p.groups.size(), 0);
         fused.ngroups = 0;
@@ -222,9 +223,10 @@ class FanSession {
     bool used_[FANOUT_SIDE + 1] = {};
 };
 
-rr_status launch_batch_plan(const BatchPlan& p, const uint8_t* dev_table, GroupLaunch how, int device,
-                            hipStream_t st, GroupFanout* fan) {
-    const Launches l(p, dev_table, how);
+// Enqueue the launches of one plan: one after another on st, or (with a fanout)
+// spread over st and the side streams.
+static rr_status enqueue(const Launches& l, const uint8_t* dev_table, GroupLaunch how, int device, hipStream_t st,
+                         GroupFanout* fan) {
     if (!fan || !fan->fork || l.count() < 2) {
         if (l.fused.ngroups) {
             hipError_t e = launch_batch_fused(l.fused, st);
@@ -244,6 +246,11 @@ rr_status launch_batch_plan(const BatchPlan& p, const uint8_t* dev_table, GroupL
     return rs != RR_OK ? rs : re;
 }
 
+rr_status launch_batch_plan(const BatchPlan& p, const uint8_t* dev_table, GroupLaunch how, int device,
+                            hipStream_t st, GroupFanout* fan) {
+    return enqueue(Launches(p, dev_table, how), dev_table, how, device, st, fan);
+}
+
 }  // namespace rr
 
 using namespace rr;
@@ -261,6 +268,7 @@ struct rr_batch {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     GroupFanout fan;      // groups run side by side on these
+    Launches launches;    // of the plan, its table in dev_table
     double tuned_us = 0.0;
 };
 
@@ -520,6 +528,7 @@ rr_status rr_batch_create(const rr_job* jobs, int njobs, int flags, rr_batch** o
     if (st == RR_OK) st = fanout_init(&b->fan);
     if (st == RR_OK) st = upload_table(b);
     if (st == RR_OK && (flags & RR_BATCH_TUNE) && !b->plan.groups.empty()) st = tune(b);
+    if (st == RR_OK) b->launches = Launches(b->plan, (const uint8_t*)b->dev_table, how_of(b));
     if (st != RR_OK) {
         if (b->dev_table) (void)hipFree(b->dev_table);
         fanout_destroy(&b->fan);
@@ -537,15 +546,14 @@ rr_status rr_batch_launch(rr_batch* b, rr_stream_t stream) {
     hipStream_t hs = (hipStream_t)stream;
     // a batch that is one launch gains nothing from a graph of one node (18 us a
     // replay of 16 small jobs against 9 us for the launch itself)
-    if (!(b->flags & RR_BATCH_GRAPH) || Launches(b->plan, (const uint8_t*)b->dev_table, how_of(b)).count() == 1)
-        return launch_batch_plan(b->plan, (const uint8_t*)b->dev_table, how_of(b), b->device, hs, fan_of(b));
+    if (!(b->flags & RR_BATCH_GRAPH) || b->launches.count() == 1)
+        return enqueue(b->launches, (const uint8_t*)b->dev_table, how_of(b), b->device, hs, fan_of(b));
     if (!b->exec) {
         if (!b->cap_stream && hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking) != hipSuccess)
             return fail(RR_ERR_HIP, "capture stream");
         hipError_t e = hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal);
         if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
-        rr_status st = launch_batch_plan(b->plan, (const uint8_t*)b->dev_table, how_of(b), b->device, b->cap_stream,
-                                         fan_of(b));
+        rr_status st = enqueue(b->launches, (const uint8_t*)b->dev_table, how_of(b), b->device, b->cap_stream, fan_of(b));
         hipGraph_t g = nullptr;
         e = hipStreamEndCapture(b->cap_stream, &g);
         if (st != RR_OK) { if (g) (void)hipGraphDestroy(g); return st; }
