@@ -410,7 +410,8 @@ rr_status rr_order_to_perm(int ndim, const int* paper_order, int* perm_out);
 /* -------------------------------------------------------------------------
  * Host-only plan introspection (no GPU needed): the canonical form and kernel
  * plan rr_permute would use for this problem, written as one line of text
- * "class=... rank=... dims=... perm=... esize_bytes=... unit=... ..." into buf.
+ * "class=... rank=... dims=... perm=... esize_bytes=... unit=... ..." into buf, with
+ * the kernel it runs where a class has several.
  * Alignment is taken from the two pointer values (which need not be valid).
  */
 /* The same for the plan rr_reorder would use (alignment from dst and from src

@@ -170,10 +170,11 @@ static hipError_t launch_tile_ug(const TileArgs& a, uint32_t grid, hipStream_t s
 }
 
 static hipError_t launch_tile(const TileArgs& a, uint32_t grid, hipStream_t st) {
-    // Records split in registers at every size measured (3 MB: 11.0 -> 6.5 us; 727 MB:
-    // 143 -> 136); tiles above 32 KiB come only from a caller's own tile option.
-    if (tile_split(a) && a.lds_bytes <= 32768) return launch_tile_split(a, grid, st);
-    if (ragged_narrow(a)) return a.unit == 1 ? launch_tile_ragged<1>(a, grid, st) : launch_tile_ragged<2>(a, grid, st);
+    switch (tile_kernel(a)) {
+        case TileKernel::split: return launch_tile_split(a, grid, st);
+        case TileKernel::ragged: return a.unit == 1 ? launch_tile_ragged<1>(a, grid, st) : launch_tile_ragged<2>(a, grid, st);
+        case TileKernel::tile: break;
+    }
     switch (a.unit * 100 + a.g) {
         case 101: return launch_tile_ug<1, 1>(a, grid, st);
         case 102: return launch_tile_ug<1, 2>(a, grid, st);

@@ -1495,15 +1495,17 @@ std::string describe(const Plan& p) {
     if (p.kind == K_WEAVE)
         o << " n=" << p.weave.n << " unit=" << p.weave.unit << " de=" << p.weave.de << " nvec=" << p.weave.nvec
           << " cached=" << p.weave.cached << " chunks=" << p.weave.chunks
-          << " batches=" << (p.weave.bpb ? p.grid / p.weave.bpb : 0);
+          << " batches=" << (p.weave.bpb ? p.grid / p.weave.bpb : 0) << " kernel=" << (p.weave.any ? "k_weave_any" : "k_weave");
     if (p.kind == K_GATHER) o << " vec=" << p.gather.wbytes << " k=" << p.gather.k << " indexed=" << (p.gather.idx != 0);
     if (p.kind == K_SELECT) o << " vec=16 stride=" << p.select.S << " m=" << p.select.M << " n=" << p.select.n;
     if (p.kind == K_TILE) {
+        static const char* kernels[] = {"k_tile", "k_tile_ragged", "k_tile_split"};
         const TileArgs& a = p.tile;
         o << " unit=" << a.unit << " g=" << a.g << " k=" << a.k << " TA=" << a.TA << " TB=" << a.TB
           << " nA=" << a.nA << " nB=" << a.nB << " win=" << a.win << " pitch=" << a.pitch
           << " lds=" << a.lds_bytes << " ntiles=" << a.ntiles << " ngrid=" << a.ngrid
-          << " tc=" << a.cO_t << " flags=" << a.flags << " order=" << (a.flags & TF_ORDER_OUT ? "out" : "in");
+          << " tc=" << a.cO_t << " flags=" << a.flags << " order=" << (a.flags & TF_ORDER_OUT ? "out" : "in")
+          << " kernel=" << kernels[(int)tile_kernel(a)];
     }
     return o.str();
 }

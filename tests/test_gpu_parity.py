@@ -522,3 +522,14 @@ def test_unaligned_run_vectors(rr):
     for dims, perm, e, so, do in big:
         d = rr.plan_describe(dims, perm, e, (1 << 20) + do, (1 << 30) + so)
         assert d["class"] == "run" and d["vec"] == "16" and d["ua"] == "1", d
+
+
+def test_the_kernel_that_the_plan_names(rr):
+    """Plans name the kernel they run; each of the single-launch tile kernels is selected
+    where it should be, and gives the oracle's bytes."""
+    for dims, perm, e, kernel in [((1001, 999), (1, 0), 1, "k_tile_ragged"), ((130, 260), (1, 0), 2, "k_tile_ragged"),
+                                  ((1001, 999), (1, 0), 4, "k_tile"), ((512, 512), (1, 0), 2, "k_tile"),
+                                  ((4, 50, 33, 3), (0, 2, 3, 1), 2, "k_tile_ragged")]:
+        _say("kernel", kernel, dims, e)
+        assert rr.plan_describe(dims, perm, e, 1 << 40, 1 << 42)["kernel"] == kernel, dims
+        check_permute(rr, dims, perm, e, 15100 + e, 0, 0)

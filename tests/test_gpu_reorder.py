@@ -105,3 +105,15 @@ def test_channel_of_rgba_image_full_size(rr):
     dims, base, rng, order, e = (16384, 16384, 4), (0, 0, 2), (16384, 16384, 1), (0, 1), 1
     assert rr.reorder_describe(dims, base, rng, order, e, 1 << 20, 1 << 30)["class"] == "select"
     check(rr, dims, base, rng, order, e, 12200)
+
+
+@pytest.mark.parametrize("base,range_,kernel", [((0, 4, 3, 0), (3, 31, 22, 3), "k_tile_split"),
+                                                ((0, 0, 0, 0), (3, 32, 128, 3), "k_tile"),
+                                                ((0, 3, 1, 0), (3, 32, 127, 3), "k_tile_split")])
+def test_reorder_record_split_kernel(rr, base, range_, kernel):
+    """Crops of records whose tiles share lines are split in registers; crops on line
+    boundaries, whose tiles write past the caches, take the general tile kernel."""
+    dims = (3, 40, 256, 3)
+    for e in (1, 2, 4):
+        assert rr.reorder_describe(dims, base, range_, (0, 3, 1, 2), e, 1 << 40, 1 << 42)["kernel"] == kernel, e
+        check(rr, dims, base, range_, (0, 3, 1, 2), e, 11500 + e)
