@@ -301,8 +301,9 @@ rr_status rr_batch_launch(rr_batch* b, rr_stream_t stream);
 rr_status rr_batch_get_info(const rr_batch* b, rr_batch_info* out);
 /* One text line per kernel group of the batch as currently planned, in the order
  * the groups are stored (and launched under RR_BATCH_SERIAL):
- *   "kernel=k_batch_tile<8,1> jobs=622 workgroups=194744 bytes=2179800000 lds=16384"
- * (bytes per side moved by the group).  Host only.  Errors: RR_ERR_INVALID_ARG
+ *   "kernel=k_batch_tile<8,1> jobs=622 workgroups=194744 bytes=2179800000 lds=16384 fused=1"
+ * (bytes per side moved by the group; fused: the group is part of the batch's one
+ * launch over several groups, whose kernel has the same bodies).  Host only.  Errors: RR_ERR_INVALID_ARG
  * (NULL argument, or buf shorter than the text; buflen counts the final NUL). */
 rr_status rr_batch_describe(const rr_batch* b, char* buf, int buflen);
 rr_status rr_batch_destroy(rr_batch* b);

@@ -300,8 +300,9 @@ class Batch:
         return {n: getattr(i, n) for n, _ in BatchInfo._fields_}
 
     def groups(self) -> list:
-        """One dict per kernel group (kernel, jobs, workgroups, bytes per side, lds),
-        in storage order (the launch order under RR_BATCH_SERIAL)."""
+        """One dict per kernel group (kernel, jobs, workgroups, bytes per side, lds, fused:
+        1 if it is part of the batch's one launch), in storage order (the launch order
+        under RR_BATCH_SERIAL)."""
         buf = ctypes.create_string_buffer(1 << 16)
         check(lib().rr_batch_describe(self.h, buf, len(buf)))
         out = []

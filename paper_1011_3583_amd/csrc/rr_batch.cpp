@@ -7,6 +7,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -590,13 +591,15 @@ rr_status rr_batch_describe(const rr_batch* b, char* buf, int buflen) {
     clear_error();
     if (!b || !buf || buflen < 1) return fail(RR_ERR_INVALID_ARG, "NULL argument");
     std::string text;
+    const std::set<const BatchGroup*> own(b->launches.single.begin(), b->launches.single.end());
     for (const BatchGroup& g : b->plan.groups) {
         std::string k;
         if (g.kind == K_COPY) k = "k_batch_copy<" + std::to_string(g.variant) + ">";
         else if (g.kind == K_RUN) k = "k_batch_run<" + std::to_string(g.variant) + ">";
         else k = "k_batch_tile<" + std::to_string(g.variant / 100) + "," + std::to_string(g.variant % 100) + ">";
         text += "kernel=" + k + " jobs=" + std::to_string(g.njobs) + " workgroups=" + std::to_string(g.total_blocks) +
-                " bytes=" + std::to_string(g.bytes) + " lds=" + std::to_string(g.lds_bytes) + "\n";
+                " bytes=" + std::to_string(g.bytes) + " lds=" + std::to_string(g.lds_bytes) +
+                " fused=" + std::to_string(own.count(&g) ? 0 : 1) + "\n";
     }
     if ((int)text.size() + 1 > buflen) return fail(RR_ERR_INVALID_ARG, "buffer too short");
     std::memcpy(buf, text.c_str(), text.size() + 1);

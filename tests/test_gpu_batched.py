@@ -365,3 +365,81 @@ def test_one_shot_table_upload_both_ways(rr, njobs):
     torch.cuda.synchronize()
     for J in sets:
         _check_all_vs_oracle(J)
+
+
+def _several_launches(rr, J):
+    """The batch keeps several launches of its own (and is not one fused launch)."""
+    b = rr.Batch(J.arr, 0)
+    groups = b.groups()
+    b.close()
+    return sum(1 for g in groups if not g["fused"]) >= 3
+
+
+def test_unfused_calls_on_two_streams_share_side_streams(rr):
+    """Batches of several launches (a micro-tile cap keeps their groups apart) fan out on
+    the side streams shared per device: calls issued alternately on two streams, each
+    after its own work on that stream, and twelve more from four host threads."""
+    import threading
+    rr.set_tile_override(max_g=2)
+    try:
+        specs = _uneven(6, 300, 9000)
+        Js = [Jobs(rr, specs, 60 + k) for k in range(6)]
+        assert _several_launches(rr, Js[0])
+        torch.cuda.synchronize()
+        streams = [torch.cuda.Stream() for _ in range(4)]
+        for k, J in enumerate(Js):
+            st = streams[k % 2]
+            _say("two streams, several launches, call", k)
+            with torch.cuda.stream(st):
+                J.dst.zero_()   # queued on this stream: the batch must run after it
+            rr.check(rr.permute_batched_raw(J.arr, len(specs), st.cuda_stream))
+        for st in streams:
+            st.synchronize()
+        for J in Js:
+            _check_all_vs_oracle(J)
+            J.dst.zero_()
+        torch.cuda.synchronize()
+        errs = []
+
+        def run(k):
+            try:
+                for _ in range(3):
+                    rr.check(rr.permute_batched_raw(Js[k].arr, len(specs), streams[k].cuda_stream))
+            except Exception as e:   # reported below, on the test's thread
+                errs.append(e)
+
+        _say("four host threads, several launches")
+        th = [threading.Thread(target=run, args=(k,)) for k in range(4)]
+        for t in th:
+            t.start()
+        for t in th:
+            t.join()
+        for st in streams:
+            st.synchronize()
+        assert not errs, errs
+        for J in Js[:4]:
+            _check_all_vs_oracle(J)
+    finally:
+        rr.set_tile_override(0, 0, None)
+
+
+@pytest.mark.parametrize("flags", [0, 1, 1 | 4])
+def test_unfused_handle_modes(rr, flags):
+    """A handle of several launches, plain, captured into a graph and with persistent
+    grids in a graph: replays with eager work between are bit-exact."""
+    rr.set_tile_override(max_g=2)
+    try:
+        specs = _uneven(7, 200, 12000)
+        J = Jobs(rr, specs, 7)
+        assert _several_launches(rr, J)
+        _say("several launches, handle flags", flags)
+        b = rr.Batch(J.arr, flags)
+        for rep in range(4):
+            J.dst.zero_()
+            torch.cuda.synchronize()
+            b.launch(torch.cuda.current_stream())
+            torch.cuda.synchronize()
+            _check_all_vs_oracle(J, sample=None if rep == 0 else 40)
+        b.close()
+    finally:
+        rr.set_tile_override(0, 0, None)
