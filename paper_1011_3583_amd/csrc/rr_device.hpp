@@ -374,19 +374,93 @@ RR_HD void copy_thread(const CopyArgs& a, uint32_t block, uint32_t nblocks, uint
 // by is the 128-byte line it fetches, and a line that several indices hit is then
 // found again in L2 or the Infinity Cache, where a streamed load leaves nothing
 // behind (random 4-byte reads of a 1 GiB table 1632 -> 1378 us for 2^26 indices, of
-// a 16 MiB one 1234 -> 958; sorted sets 0.95-1.37x).  A range walks its lines once
-// and streams them.  Returns how many indices fell outside the source.
-template <int W, bool IDX>
-RR_HD uint32_t gather_body(const GatherArgs& a, uint64_t block, uint64_t nblocks, uint32_t tid) {
+// a 256 MiB one 1594 -> 1312; fewer than 2^20 of 8 bytes up to 5 % slower).  A range
+// walks its lines once and streams them, and so does a wave whose indices ascend where
+// the table exceeds the Infinity Cache: the lines of a sorted set are not met again
+// (sorted sets of a 1 GiB table ran at 0.92-0.99x through the caches and run at
+// 0.99-1.03x streamed; of up to 256 MiB 1.0-1.1x through the caches).  Returns how
+// many indices fell outside the source.
+
+// Keeps the compiler from moving memory accesses across this point.
+RR_HD void compiler_fence() {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" ::: "memory");
+#endif
+}
+
+// Whether the indices of a wave ascend.
+RR_HD bool wave_ascends(int64_t s) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    // the lane below's words (wave_shr:1; lane 0 keeps its own)
+    const int l = (int)(uint32_t)(uint64_t)s, h = (int)(uint32_t)((uint64_t)s >> 32);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(l, l, 0x138, 0xf, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(h, h, 0x138, 0xf, 0xf, false);
+    return __all((int64_t)(((uint64_t)hi << 32) | lo) <= s);
+#else
+    (void)s;
+    return false;
+#endif
+}
+
+// Read and store the four elements of one step (source positions at; S: streamed
+// reads).  Returns how many of them lie outside the source.
+template <int W, bool S>
+RR_HD uint32_t gather_move(const GatherArgs& a, uint64_t base, uint64_t n, const int64_t (&at)[4]) {
     constexpr int NW = NWords<W>::value;
     const uint8_t* src = reinterpret_cast<const uint8_t*>(a.src);
     uint8_t* dst = reinterpret_cast<uint8_t*>(a.dst);
+    uint32_t nbad = 0;
+    int64_t s[4];
+    bool ok[4], valid[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        ok[u] = base + (uint64_t)u * NT < n;
+        valid[u] = ok[u] && at[u] >= 0 && at[u] < a.src_count;
+        nbad += ok[u] && !valid[u];
+        s[u] = valid[u] ? at[u] : 0;   // element 0 is read instead and discarded
+    }
+    const bool any_src = a.src_count > 0;
+    if (a.k == 1) {
+        uint32_t v[4][NW];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (any_src) gload<W, S>(src + (uint64_t)s[u] * W, v[u]);
+            else
+#pragma unroll
+                for (int q = 0; q < NW; ++q) v[u][q] = 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (!valid[u])
+#pragma unroll
+                for (int q = 0; q < NW; ++q) v[u][q] = 0;
+            if (ok[u]) gstore<W>(dst + (base + (uint64_t)u * NT) * W, v[u]);
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (!ok[u]) continue;
+            const uint8_t* ps = src + (uint64_t)s[u] * a.esize;
+            uint8_t* pd = dst + (base + (uint64_t)u * NT) * a.esize;
+            for (uint32_t q = 0; q < a.k; ++q) {
+                uint32_t v[NW];
+#pragma unroll
+                for (int c = 0; c < NW; ++c) v[c] = 0;
+                if (valid[u]) gload<W, S>(ps + q * W, v);
+                gstore<W>(pd + q * W, v);
+            }
+        }
+    }
+    return nbad;
+}
+
+template <int W, bool IDX, bool LARGE>
+RR_HD uint32_t gather_body(const GatherArgs& a, uint64_t block, uint64_t nblocks, uint32_t tid) {
     const uint8_t* idx = reinterpret_cast<const uint8_t*>(a.idx);
     const uint64_t n = (uint64_t)a.count;   // >= 1 when launched
     uint32_t nbad = 0;
     for (uint64_t base = block * NT * 4 + tid; base < n; base += nblocks * NT * 4) {
         int64_t s[4];
-        bool ok[4], valid[4];
         uint32_t w[4][2];
         if constexpr (IDX) {
 #pragma unroll
@@ -396,53 +470,27 @@ RR_HD uint32_t gather_body(const GatherArgs& a, uint64_t block, uint64_t nblocks
             }
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint64_t i = base + (uint64_t)u * NT;
-            ok[u] = i < n;
-            s[u] = IDX ? (int64_t)(((uint64_t)w[u][1] << 32) | w[u][0]) : a.start + (int64_t)i * a.stride;
-            valid[u] = ok[u] && s[u] >= 0 && s[u] < a.src_count;
-            nbad += ok[u] && !valid[u];
-            if (!valid[u]) s[u] = 0;   // element 0 is read instead and discarded
-        }
-        const bool any_src = a.src_count > 0;
-        if (a.k == 1) {
-            uint32_t v[4][NW];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (any_src) gload<W, !IDX>(src + (uint64_t)s[u] * W, v[u]);
-                else
-#pragma unroll
-                    for (int q = 0; q < NW; ++q) v[u][q] = 0;
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (!valid[u])
-#pragma unroll
-                    for (int q = 0; q < NW; ++q) v[u][q] = 0;
-                if (ok[u]) gstore<W>(dst + (base + (uint64_t)u * NT) * W, v[u]);
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (!ok[u]) continue;
-                const uint8_t* ps = src + (uint64_t)s[u] * a.esize;
-                uint8_t* pd = dst + (base + (uint64_t)u * NT) * a.esize;
-                for (uint32_t q = 0; q < a.k; ++q) {
-                    uint32_t v[NW];
-#pragma unroll
-                    for (int c = 0; c < NW; ++c) v[c] = 0;
-                    if (valid[u]) gload<W, !IDX>(ps + q * W, v);
-                    gstore<W>(pd + q * W, v);
-                }
+        for (int u = 0; u < 4; ++u)
+            s[u] = IDX ? (int64_t)(((uint64_t)w[u][1] << 32) | w[u][0])
+                       : a.start + (int64_t)(base + (uint64_t)u * NT) * a.stride;
+        if constexpr (IDX && LARGE) {
+            if (wave_ascends(s[0])) {
+                compiler_fence();   // or the two flavours of load are merged into cached ones
+                nbad += gather_move<W, true>(a, base, n, s);
+                continue;
             }
         }
+        nbad += gather_move<W, !IDX>(a, base, n, s);
     }
     return nbad;
 }
 
-template <int W>
+// LARGE: an index set of a source above GATHER_CACHED_BYTES (kernels of their own: the
+// test for ascending indices would cost the others up to 4 %).
+template <int W, bool LARGE = false>
 RR_HD uint32_t gather_thread(const GatherArgs& a, uint64_t block, uint64_t nblocks, uint32_t tid) {
-    return a.idx ? gather_body<W, true>(a, block, nblocks, tid) : gather_body<W, false>(a, block, nblocks, tid);
+    if constexpr (LARGE) return gather_body<W, true, true>(a, block, nblocks, tid);
+    return a.idx ? gather_body<W, true, false>(a, block, nblocks, tid) : gather_body<W, false, false>(a, block, nblocks, tid);
 }
 
 // ----------------------------------------------------------------- 2-D stencil

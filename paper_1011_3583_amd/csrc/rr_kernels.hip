@@ -51,9 +51,9 @@ __global__ __launch_bounds__(NT) void k_stencil(const StencilArgs a) {
     stencil_compute<R, SHAPE, TH>(a, tile, lds, threadIdx.x);
 }
 
-template <int W>
+template <int W, bool LARGE>
 __global__ __launch_bounds__(NT) void k_gather(const GatherArgs a) {
-    const uint32_t nbad = gather_thread<W>(a, blockIdx.x, gridDim.x, threadIdx.x);
+    const uint32_t nbad = gather_thread<W, LARGE>(a, blockIdx.x, gridDim.x, threadIdx.x);
     if (nbad && a.bad) atomicAdd(reinterpret_cast<unsigned long long*>(a.bad), (unsigned long long)nbad);
 }
 
@@ -232,6 +232,13 @@ static hipError_t launch_select_r(const SelectArgs& a, uint32_t grid, hipStream_
     return hipGetLastError();
 }
 
+template <int W>
+static hipError_t launch_gather(const GatherArgs& a, uint32_t grid, hipStream_t st) {
+    if (a.large) hipLaunchKernelGGL((k_gather<W, true>), dim3(grid), dim3(NT), 0, st, a);
+    else hipLaunchKernelGGL((k_gather<W, false>), dim3(grid), dim3(NT), 0, st, a);
+    return hipGetLastError();
+}
+
 static hipError_t launch_select(const SelectArgs& a, uint32_t grid, hipStream_t st) {
     switch (a.R) {
         case 1: return launch_select_r<1>(a, grid, st);
@@ -318,11 +325,11 @@ hipError_t launch_plan(const Plan& p, hipStream_t st) {
             return launch_weave(p.weave, p.grid, st);
         case K_GATHER:
             switch (p.gather.wbytes) {
-                case 16: hipLaunchKernelGGL(k_gather<16>, dim3(p.grid), dim3(NT), 0, st, p.gather); break;
-                case 8: hipLaunchKernelGGL(k_gather<8>, dim3(p.grid), dim3(NT), 0, st, p.gather); break;
-                case 4: hipLaunchKernelGGL(k_gather<4>, dim3(p.grid), dim3(NT), 0, st, p.gather); break;
-                case 2: hipLaunchKernelGGL(k_gather<2>, dim3(p.grid), dim3(NT), 0, st, p.gather); break;
-                default: hipLaunchKernelGGL(k_gather<1>, dim3(p.grid), dim3(NT), 0, st, p.gather); break;
+                case 16: return launch_gather<16>(p.gather, p.grid, st);
+                case 8: return launch_gather<8>(p.gather, p.grid, st);
+                case 4: return launch_gather<4>(p.gather, p.grid, st);
+                case 2: return launch_gather<2>(p.gather, p.grid, st);
+                default: return launch_gather<1>(p.gather, p.grid, st);
             }
             return hipGetLastError();
     }

@@ -416,6 +416,7 @@ void plan_gather(uint64_t dst, uint64_t src, uint64_t idx, uint64_t bad, int64_t
     a.src = src; a.dst = dst; a.idx = idx; a.bad = bad;
     a.count = count; a.src_count = src_count; a.start = start; a.stride = stride;
     a.esize = (uint32_t)esize; a.wbytes = W; a.k = (uint32_t)esize / W;
+    a.large = idx && src_count > GATHER_CACHED_BYTES / esize ? 1u : 0u;
     uint64_t per_block = (uint64_t)NT * 4;
     uint64_t g = ((uint64_t)count + per_block - 1) / per_block;
     if (g < 1) g = 1;
@@ -1496,7 +1497,7 @@ std::string describe(const Plan& p) {
         o << " n=" << p.weave.n << " unit=" << p.weave.unit << " de=" << p.weave.de << " nvec=" << p.weave.nvec
           << " cached=" << p.weave.cached << " chunks=" << p.weave.chunks
           << " batches=" << (p.weave.bpb ? p.grid / p.weave.bpb : 0) << " kernel=" << (p.weave.any ? "k_weave_any" : "k_weave");
-    if (p.kind == K_GATHER) o << " vec=" << p.gather.wbytes << " k=" << p.gather.k << " indexed=" << (p.gather.idx != 0);
+    if (p.kind == K_GATHER) o << " vec=" << p.gather.wbytes << " k=" << p.gather.k << " indexed=" << (p.gather.idx != 0) << " large=" << p.gather.large;
     if (p.kind == K_SELECT) o << " vec=16 stride=" << p.select.S << " m=" << p.select.M << " n=" << p.select.n;
     if (p.kind == K_TILE) {
         static const char* kernels[] = {"k_tile", "k_tile_ragged", "k_tile_split"};

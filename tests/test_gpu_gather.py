@@ -74,3 +74,21 @@ def test_gather_large(rr):
             j = dict(src_count=n, esize=e, start=start, stride=stride, count=cnt, input=x)
             got, _ = run_gpu(rr, j)
             assert np.array_equal(got, gather_ref(j)[0])
+
+
+@pytest.mark.parametrize("e", [1, 3, 4, 16])
+def test_gather_above_the_infinity_cache(rr, e):
+    """Tables above 256 MiB, whose ascending waves read past the caches: sorted sets (with
+    repeats), random ones and mixtures within a wave, indices out of range among them,
+    counts that end inside a wave."""
+    n = (257 << 20) // e
+    x = rr_synth.random_bytes(90 + e, n * e)
+    g = rr_synth.rng(91)
+    up = np.sort(g.integers(0, n, 70_003)).astype(np.int64)
+    for idx in (up, up[::-1].copy(), g.integers(-5, n + 5, 70_001).astype(np.int64),
+                np.where(np.arange(70_003) // 40 % 2 == 0, up, up[::-1]), np.repeat(up[:9000], 7),
+                np.concatenate([[-1, -1], up[:126], [n, n + 7]]), up[:1]):
+        j = dict(src_count=n, esize=e, idx=np.ascontiguousarray(idx), input=x)
+        got, nbad = run_gpu(rr, j)
+        ref, ref_bad = gather_ref(j)
+        assert nbad == ref_bad and np.array_equal(got, ref)
