@@ -148,7 +148,9 @@ static uint64_t group_cost(const BatchGroup& g) {
 // its groups after one another where the streams overlap them.  Both measured on
 // handles, a launch per group against fused: 16 jobs of 1 MB 93 / 9 us, 256 jobs
 // of 77 MB 101 / 40, 215 jobs of 185 MB 113 / 78, 300 jobs of 589 MB 276 / 274,
-// 600 jobs of 1.26 GB 553 / 568, 4096 jobs of 7.5 GB 3145 / 3556 us.
+// 600 jobs of 1.26 GB 553 / 568, 4096 jobs of 7.5 GB 3145 / 3556 us.  The chunks of a
+// pipelined call decide each for itself: 2100 jobs of 870 MB 902 / 708 us, 4096 jobs of
+// 1.7 GB 1491 / 1305, of 7.5 GB 3226 / 3239.
 constexpr uint64_t FUSED_MAX_BYTES = 512ull << 20;
 
 // The launches of one batch plan: the fused launch first (if any), then the groups

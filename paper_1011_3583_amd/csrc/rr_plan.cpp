@@ -790,8 +790,8 @@ static rr_status finish_tile(TileArgs& a, int U, int G, int k, uint64_t row_alig
 // Workgroups per CU.  A CU holds eight tile workgroups, and eight times 256 tiles in
 // flight touch twice the 4 MB L2 of each XCD: the two parts of a line that tiles share
 // then meet in HBM instead.  On large grids four run faster; asking for 40 KiB of a
-// CU's 160 KiB of LDS holds the launch there.  Measured, eight against four, on 900
-// random shapes of 120 MB to 2 GB (tiles of 14 KiB and more with whole lines on both
+// CU's 160 KiB of LDS holds the launch there.  Measured, eight against four, on 1400
+// random shapes of 100 MB to 2 GB (tiles of 14 KiB and more with whole lines on both
 // sides, neither side held whole; geometric mean and range of the gain):
 //   sharing lines: 1-byte units from 12288 tiles 1.10x (0.94 to 1.51), 2-byte 1.10x
 //     (0.99 to 1.41); both 0.80 to 1.25x below.  16-byte ones from 16384 tiles 1.03x
@@ -800,21 +800,38 @@ static rr_status finish_tile(TileArgs& a, int U, int G, int k, uint64_t row_alig
 //     Elements of several units 0.88 to 1.0x: left at eight;
 //   8-byte units from 65536 tiles, sharing lines 1.035x (0.94 to 1.15) or not 1.02x
 //     (0.98 to 1.09) up to three axes; below that 0.88 to 1.05x;
-//   16-byte units that share no lines, up to three axes, from 32768 tiles: 1.03x (0.975
-//     to 1.125); other units that share none 0.88 to 1.03x.
+//   16-byte units that share no lines, up to three axes, from 32768 tiles: 1.03x (0.96
+//     to 1.125);
+//   rows that share no lines but lie at pitches of large powers of two, which pile up
+//     on few HBM channels, up to three axes: 8-byte units at multiples of 2 KiB from
+//     24576 tiles 1.016x (0.95 to 1.065; 0.995x from 8192 to 24576), 16-byte ones
+//     likewise (1.045x, three shapes of 24576), 4-byte units in
+//     three-axis problems at multiples of 1 KiB from 16384 tiles 1.013x (0.98 to 1.07;
+//     1.003x from 8192 to 16384, 0.985x at 512 bytes); others that share none 0.88 to
+//     1.03x.
 // Tiles under 14 KiB or with short rows need the waves to hide latency (23-element
 // rows of 4 bytes 164 -> 208 us; 2-byte ones at five per CU 0.74 to 1.1x).
-static uint32_t tile_reserve(const TileArgs& a, int rank, const TileOptions& opt) {
+//   pitches : OR of the byte strides of every axis but the fastest, both sides
+static uint32_t tile_reserve(const TileArgs& a, int rank, uint64_t pitches, const TileOptions& opt) {
     if (opt.batched || a.k != 1 || (a.flags & TF_STACK) || a.grid_aO < 0 || a.grid_bO < 0) return 0;
     if (a.lds_bytes < 14336 || a.TA * a.R < 128 || a.TB * a.R < 128) return 0;
     const bool share = (a.flags & TF_XCD) != 0;
     uint32_t from = 16384;
-    bool ok = share;
+    bool ok = share || rank <= 3;
     switch (a.unit) {
-        case 1: case 2: from = 12288; break;
-        case 4: ok = share && (a.g > 1 || rank == 2); break;
-        case 8: from = 65536; ok = share || rank <= 3; break;
-        default: from = share ? 16384 : 32768; ok = share || rank <= 3; break;
+        case 1: case 2:
+            ok = share;
+            from = 12288;
+            break;
+        case 4:
+            ok = share ? a.g > 1 || rank == 2 : rank == 3 && pitches % 1024 == 0;
+            break;
+        case 8:
+            from = !share && pitches % 2048 == 0 ? 24576 : 65536;
+            break;
+        default:
+            from = share ? 16384 : pitches % 2048 == 0 ? 24576 : 32768;
+            break;
     }
     return ok && a.ntiles >= from ? TF_FOUR_PER_CU : 0;
 }
@@ -1264,7 +1281,9 @@ static rr_status plan_tile_as(uint64_t dst, uint64_t src, const Canon& c, const 
     }
     if (a.ngrid >= 2 && (opt.diag == 1 || (opt.diag == -1 && diag_by_default(c)))) a.flags |= TF_DIAG;
     if (order_out) a.flags |= TF_ORDER_OUT;
-    a.flags |= tile_reserve(a, r, opt);
+    uint64_t pitches = row_starts;
+    for (int q = 0; q < r; ++q) if (q != b1) pitches |= (uint64_t)(sout_el[q] * R);
+    a.flags |= tile_reserve(a, r, pitches, opt);
     p->grid = a.ntiles;
     p->bytes = (uint64_t)c.total_bytes;
     return RR_OK;

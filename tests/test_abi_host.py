@@ -584,7 +584,9 @@ RESERVE_CASES = [
     ((1812, 222, 47, 18), (1, 2, 0, 3), 1, False),                             # elements of several units
     ((33, 236, 122, 92), (3, 1, 0, 2), 2, False),                              # 2-byte tiles under 14 KiB
     ((5296, 8608), (1, 0), 8, False), ((16384, 16384), (1, 0), 8, True),       # 8-byte units: by the grid
-    ((512, 512, 256), (2, 1, 0), 4, False), ((8192, 8192), (1, 0), 4, False),  # no shared lines
+    ((512, 512, 256), (2, 1, 0), 4, True), ((512, 512, 224), (2, 1, 0), 4, False), ((512, 416, 512), (2, 1, 0), 4, True),
+    ((512, 512, 192), (2, 1, 0), 4, False), ((8192, 8192), (1, 0), 4, False), ((6400, 8192), (1, 0), 8, True),   # no shared lines: by pitch
+    ((6400, 8128), (1, 0), 8, False), ((4096, 8192), (1, 0), 8, False),
     ((8192, 8192), (1, 0), 16, True), ((4096, 4096), (1, 0), 16, False), ((64, 64, 64, 64, 8), (4, 3, 2, 1, 0), 16, False),
 ]
 
