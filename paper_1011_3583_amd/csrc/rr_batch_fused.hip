@@ -35,9 +35,10 @@ __device__ __forceinline__ void fused_copy(const uint8_t* table, const FusedGrou
 // its group among the directory's starts (kernel arguments, scalar compares), then
 // its job and tile as in k_batch_*, and branches uniformly to that body.  The
 // bodies are those of the batch kernels, so the launch needs the registers of the
-// widest one: 53 VGPRs (the table pointer is __restrict__, so job arguments are
-// scalar loads; without it they took vector registers and spilled), held to eight
-// waves per SIMD.  16 jobs / 1 MB: 93 -> 9 us; 256 jobs / 77 MB: 101 -> 40 us.
+// widest one: 57 VGPRs (the table pointer is __restrict__, so job arguments are
+// scalar loads; without it they took vector registers and spilled) and, past the
+// scalar registers, 258 scalar values in vector-register lanes; asked for seven waves
+// per SIMD it gets eight.  16 jobs / 1 MB: 93 -> 9 us; 256 jobs / 77 MB: 101 -> 40 us.
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(7, 8)))
 void k_batch_fused(const FusedArgs f, const uint8_t* __restrict__ table) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];

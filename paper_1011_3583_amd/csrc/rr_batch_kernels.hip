@@ -12,12 +12,14 @@
 
 namespace rr {
 
-// Register budget of the batch tile kernels: eight waves per SIMD.  At the
-// compiler's own choice the job lookups of a batch workgroup take these kernels
-// a few scalar registers past the eight-wave limit (seven waves); held to eight
-// they keep the excess in vector-register lanes, and the 4096-job batch ran
-// 2-4 % faster.  The two largest micro-tiles and the 2-byte G = 1 kernel would
-// spill vector registers to memory at that budget and keep the compiler's choice.
+// Register budget of the batch tile kernels: eight waves per SIMD.  The job lookups
+// and arguments of a batch workgroup take more scalar registers than eight waves
+// leave; held to eight the kernels keep the excess in vector-register lanes (103-145
+// values, the G = 1 kernels of 1-, 4- and 8-byte units 225-255: they hold the segment and
+// word-wise paths as well, 176-184 without), and the 4096-job batch ran 2-4 % faster
+// than at the seven waves of the compiler's own choice.  The two largest micro-tiles and
+// the 2-byte G = 1 kernel would spill vector registers to memory at that budget and
+// keep the compiler's choice.
 template <int U, int G>
 constexpr int batch_tile_waves() { return (U == 1 && G == 16) || (U == 2 && (G == 8 || G == 1)) ? 1 : 8; }
 

@@ -6,11 +6,12 @@
 
 namespace rr {
 
-// Crops of interleaved records to planes (and de-interlaces off 16-byte boundaries
-// below the register path's size).  Bound by LDS instructions before: every output
-// byte was a read of its own.  Here an output vector is one 16-byte read and its
-// share of a register split.  A kernel per record length, so the split is
-// compile-time byte permutes.
+// Crops of interleaved records to planes, and permutes of that form, whose tiles share
+// 128-byte lines (tiles that do not, and de-interlaces to separate planes, stream their
+// output and take k_tile).  Bound by LDS instructions before: every output byte was a
+// read of its own.  Here an output vector is one 16-byte read and its share of a
+// register split.  A kernel per record length, so the split is compile-time byte
+// permutes.
 // MI355X, RGB crops to planes, through write_ragged -> here: 224x224 of 256 u8
 // images of 256x256 (77 MB, 12 us at the copy rate; short of that by the launch and
 // one read-then-write round per workgroup) 26.2 -> 18.2 us; 30 MB 19.1 -> 14.9; 3.4 MB 11.0 -> 6.5; 727 MB of floats 143 -> 136
