@@ -372,14 +372,14 @@ RR_HD void copy_thread(const CopyArgs& a, uint32_t block, uint32_t nblocks, uint
 // (results masked afterwards) so the four of each kind are in flight together.
 // An index set (IDX) reads its elements through the caches: what a read is bound
 // by is the 128-byte line it fetches, and a line that several indices hit is then
-// found again in L2 or the Infinity Cache, where a streamed load leaves nothing
-// behind (random 4-byte reads of a 1 GiB table 1632 -> 1378 us for 2^26 indices, of
-// a 256 MiB one 1594 -> 1312; fewer than 2^20 of 8 bytes up to 5 % slower).  A range
-// walks its lines once and streams them, and so does a wave whose indices ascend where
-// the table exceeds the Infinity Cache: the lines of a sorted set are not met again
-// (sorted sets of a 1 GiB table ran at 0.92-0.99x through the caches and run at
-// 0.99-1.03x streamed; of up to 256 MiB 1.0-1.1x through the caches).  Returns how
-// many indices fell outside the source.
+// found again in the Infinity Cache, where a streamed load leaves nothing behind
+// (random 4-byte reads of a 1 GiB table 1632 -> 1378 us for 2^26 indices, with as many
+// lines leaving L2; of a 256 MiB one 1594 -> 1312; fewer than 2^20 of 8 bytes up to 5 %
+// slower).  A range walks its lines once and streams them, and so does a wave whose
+// indices ascend where the table exceeds the Infinity Cache: the lines of a sorted set
+// are not met again (sorted sets of a 1 GiB table ran at 0.92-0.99x through the caches
+// and run at 0.99-1.03x streamed; of up to 256 MiB 1.0-1.1x through the caches).
+// Returns how many indices fell outside the source.
 
 // Keeps the compiler from moving memory accesses across this point.
 RR_HD void compiler_fence() {

@@ -918,9 +918,9 @@ static double walk_cost(const Canon& c, int U, const int* pm, const bool* inA, c
 // transposed word by word (write_ragged_narrow), its segments are gathered from eight
 // or more LDS banks.  Measured, micro-tile against G = 1: 90 shapes of padded rows of 1
 // to 400 MB 0.95-2.5x, 1.25x in geometric mean (1032 x 1878 of 1 byte 13.1 -> 6.4 us),
-// but 0.82-1.03x for rows of 16, 40 and 56 bytes (32 and 48: 1.2-1.49x); segments 1.08-1.7x where their lanes lie an odd multiple of
-// 32 bytes apart, 0.4-1.27x elsewhere; rows read flat 0.49-0.95x (400000 bytes as rows
-// of 20: 5.5 -> 11.3 us).
+// but 0.82-1.03x for rows of 16, 40 and 56 bytes (32 and 48: 1.2-1.49x); segments
+// 1.08-1.7x where their lanes lie an odd multiple of 32 bytes apart, 0.4-1.27x
+// elsewhere; rows read flat 0.49-0.95x (400000 bytes as rows of 20: 5.5 -> 11.3 us).
 static bool narrow_pays(const TileArgs& a) {
     if (a.flags & TF_STACK) return false;
     if (a.flags & TF_IN_SEG) return (16 / a.unit * a.pitch) % 64 != 0;
