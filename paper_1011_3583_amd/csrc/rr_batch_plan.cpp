@@ -242,8 +242,9 @@ rr_status plan_batch(const rr_job* jobs, int njobs, const TileOptions& opt, Batc
     auto lo_of = [&](int t) { return (int)((int64_t)njobs * t / nt); };
     std::vector<int> micro_end((size_t)nt);   // a slice's jobs before this one kept micro-tiles
     auto slice = [&](int t) {
-        int kept = lo_of(t);
-        for (int i = kept; i < lo_of(t + 1); ++i) {
+        const int lo = lo_of(t), hi = lo_of(t + 1);
+        int kept = lo;
+        for (int i = lo; i < hi; ++i) {
             const bool as_rows = rows.load(std::memory_order_relaxed);
             const rr_status st = plan_job(jobs[i], opt, &plans[i], &whys[(size_t)t], as_rows);
             if (st != RR_OK) { sts[(size_t)t] = st; bad[(size_t)t] = i; return; }

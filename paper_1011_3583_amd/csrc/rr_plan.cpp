@@ -31,8 +31,7 @@ namespace rr {
 
 Magic make_magic(uint32_t d) {
     if (d == 0) d = 1;
-    uint32_t l = 0;
-    while ((uint64_t(1) << l) < d) ++l;
+    const uint32_t l = d > 1 ? 32u - (uint32_t)__builtin_clz(d - 1) : 0;   // 2^l >= d
     uint64_t mul = ((uint64_t(1) << 32) * ((uint64_t(1) << l) - d)) / d + 1;
     return Magic{(uint32_t)mul, l};
 }
@@ -1136,18 +1135,16 @@ static rr_status plan_tile_as(uint64_t dst, uint64_t src, const Canon& c, const 
             auto consider = [&](int64_t ta) {
                 const int64_t row = innerB * ((innerA * ta * R + 15) / 16 * 16);
                 const int64_t fit = soft_lds / row;   // B extent that fits the soft size
-                int64_t tb;
-                if (fit >= d[bO] && wholeB_ok) {
-                    tb = d[bO];
-                } else {
-                    const int64_t cap = std::min<int64_t>(fit, d[bO] - 1) / qB * qB;
+                int64_t tb = d[bO], n = cdiv(d[aO], ta);
+                if (fit < d[bO] || !wholeB_ok) {
+                    const int64_t cap = std::min<int64_t>(fit, d[bO] - 1) & -qB;   // qB is a power of two
                     if (cap < qB) return;
-                    tb = split(d[bO], cdiv(d[bO], cap), qB, false);
-                    if (tb == 0) return;
+                    const int64_t pieces = cdiv(d[bO], cap);   // of the even split too: it is at most cap
+                    n *= pieces;
+                    if (n >= best) return;
+                    tb = split(d[bO], pieces, qB, false);
                 }
-                if (tb < minB || lds_of(ta, tb) > soft_lds) return;
-                const int64_t n = cdiv(d[aO], ta) * cdiv(d[bO], tb);
-                if (n < best) { best = n; bestA = ta; bestB = tb; }
+                if (n < best && tb >= minB) { best = n; bestA = ta; bestB = tb; }
             };
             // A extents that leave B at least minB rows: the whole axis (where
             // allowed), then every multiple of qA from the longest down (longer
