@@ -415,7 +415,7 @@ void plan_gather(uint64_t dst, uint64_t src, uint64_t idx, uint64_t bad, int64_t
     a.src = src; a.dst = dst; a.idx = idx; a.bad = bad;
     a.count = count; a.src_count = src_count; a.start = start; a.stride = stride;
     a.esize = (uint32_t)esize; a.wbytes = W; a.k = (uint32_t)esize / W;
-    a.large = idx && src_count > GATHER_CACHED_BYTES / esize ? 1u : 0u;
+    a.large = idx && count > GATHER_CACHED_COUNT && src_count > GATHER_CACHED_BYTES / esize ? 1u : 0u;
     uint64_t per_block = (uint64_t)NT * 4;
     uint64_t g = ((uint64_t)count + per_block - 1) / per_block;
     if (g < 1) g = 1;

@@ -78,9 +78,8 @@ def test_gather_large(rr):
 
 @pytest.mark.parametrize("e", [1, 3, 4, 16])
 def test_gather_above_the_infinity_cache(rr, e):
-    """Tables above 256 MiB, whose ascending waves read past the caches: sorted sets (with
-    repeats), random ones and mixtures within a wave, indices out of range among them,
-    counts that end inside a wave."""
+    """Tables above 256 MiB: sorted sets (with repeats), random ones and mixtures within
+    a wave, indices out of range among them, counts that end inside a wave."""
     n = (257 << 20) // e
     x = rr_synth.random_bytes(90 + e, n * e)
     g = rr_synth.rng(91)
@@ -88,6 +87,23 @@ def test_gather_above_the_infinity_cache(rr, e):
     for idx in (up, up[::-1].copy(), g.integers(-5, n + 5, 70_001).astype(np.int64),
                 np.where(np.arange(70_003) // 40 % 2 == 0, up, up[::-1]), np.repeat(up[:9000], 7),
                 np.concatenate([[-1, -1], up[:126], [n, n + 7]]), up[:1]):
+        j = dict(src_count=n, esize=e, idx=np.ascontiguousarray(idx), input=x)
+        got, nbad = run_gpu(rr, j)
+        ref, ref_bad = gather_ref(j)
+        assert nbad == ref_bad and np.array_equal(got, ref)
+
+
+@pytest.mark.parametrize("e", [1, 3, 4, 16])
+def test_gather_of_many_above_the_infinity_cache(rr, e):
+    """More than 2^20 indices of a table above 256 MiB, whose ascending waves read past
+    the caches: the same kinds of set around and above that count."""
+    n = (257 << 20) // e
+    x = rr_synth.random_bytes(92 + e, n * e)
+    g = rr_synth.rng(93)
+    up = np.sort(g.integers(0, n, (1 << 20) + 70_003)).astype(np.int64)
+    half = np.arange(up.size) // 40 % 2 == 0
+    for idx in (up, up[::-1].copy(), g.integers(-5, n + 5, up.size).astype(np.int64), np.where(half, up, up[::-1]),
+                np.concatenate([[-1, -1], up, [n, n + 7]]), up[:1 << 20], up[:(1 << 20) + 1]):
         j = dict(src_count=n, esize=e, idx=np.ascontiguousarray(idx), input=x)
         got, nbad = run_gpu(rr, j)
         ref, ref_bad = gather_ref(j)
