@@ -789,16 +789,25 @@ static rr_status finish_tile(TileArgs& a, int U, int G, int k, uint64_t row_alig
 // Workgroups per CU.  A CU holds eight tile workgroups, and eight times 256 tiles in
 // flight touch twice the 4 MB L2 of each XCD: the two parts of a line that tiles share
 // then meet in HBM instead.  On large grids four run faster; asking for 40 KiB of a
-// CU's 160 KiB of LDS holds the launch there.  Measured, eight against four, on 1400
-// random shapes of 100 MB to 2 GB (tiles of 14 KiB and more with whole lines on both
-// sides, neither side held whole; geometric mean and range of the gain):
-//   sharing lines: 1-byte units from 12288 tiles 1.10x (0.94 to 1.51), 2-byte 1.10x
-//     (0.99 to 1.41); both 0.80 to 1.25x below.  16-byte ones from 16384 tiles 1.03x
-//     (0.98 to 1.12), 0.91 to 1.04x below.  4-byte ones from 16384 tiles in two-axis
-//     problems or with micro-tiles 1.04x (0.98 to 1.15), 0.84 to 1.1x otherwise.
-//     Elements of several units 0.88 to 1.0x: left at eight;
-//   8-byte units from 65536 tiles, sharing lines 1.035x (0.94 to 1.15) or not 1.02x
-//     (0.98 to 1.09) up to three axes; below that 0.88 to 1.05x;
+// CU's 160 KiB of LDS holds the launch there.  Measured, eight against four, on 4900
+// random shapes of 50 MB to 1 GB that share lines and 500 that do not (tiles of 14 KiB
+// and more with whole lines on both sides, neither side held whole; geometric mean of
+// the gain, a tenth of the shapes below and above the two figures behind it):
+//   sharing lines:
+//     1- and 2-byte units from 8192 tiles 1.12x (1.02, 1.25), 1.0x from 6000, 0.92x
+//     below.  Problems of three axes and more whose tiles are on average under three
+//     quarters full in input order 0.88 to 1.0x, or under half in output order 0.9 to
+//     1.0x; a side of several axes 0.93 to 1.0x (0.76 at worst) but for the input's in
+//     output order;
+//     4- and 16-byte ones from 10240 tiles 1.035x (0.98, 1.09), 0.99x below;
+//     8-byte ones, input order from 10240 tiles 1.04x (1.0, 1.08); output order with
+//     micro-tiles 1.025x (1.0, 1.06), as G = 1 rows from 24576 1.007x (0.98, 1.03), 0.97
+//     to 0.99x below;
+//     G = 1 rows of 4- and 8-byte units where the slowest axis stays, each transpose
+//     being small, 0.97x, and in more than three axes 1.0x: left at eight, as are
+//     elements of several units (0.88 to 1.0x);
+//   8-byte units that share no lines, up to three axes, from 65536 tiles 1.02x (0.98 to
+//     1.09); below that 0.88 to 1.05x;
 //   16-byte units that share no lines, up to three axes, from 32768 tiles: 1.03x (0.96
 //     to 1.125);
 //   rows that share no lines but lie at pitches of large powers of two, which pile up
@@ -810,26 +819,32 @@ static rr_status finish_tile(TileArgs& a, int U, int G, int k, uint64_t row_alig
 //     1.03x.
 // Tiles under 14 KiB or with short rows need the waves to hide latency (23-element
 // rows of 4 bytes 164 -> 208 us; 2-byte ones at five per CU 0.74 to 1.1x).
+//   kept    : whether the slowest axis is the output's slowest too
 //   pitches : OR of the byte strides of every axis but the fastest, both sides
-static uint32_t tile_reserve(const TileArgs& a, int rank, uint64_t pitches, const TileOptions& opt) {
+static uint32_t tile_reserve(const TileArgs& a, const Canon& c, bool kept, uint64_t pitches, const TileOptions& opt) {
     if (opt.batched || a.k != 1 || (a.flags & TF_STACK) || a.grid_aO < 0 || a.grid_bO < 0) return 0;
     if (a.lds_bytes < 14336 || a.TA * a.R < 128 || a.TB * a.R < 128) return 0;
-    const bool share = (a.flags & TF_XCD) != 0;
+    const bool share = (a.flags & TF_XCD) != 0, out_order = (a.flags & TF_ORDER_OUT) != 0;
+    const int rank = c.rank;
+    const bool rows_gain = a.g > 1 || rank == 2 || (rank == 3 && !kept);   // 4- and 8-byte units
+    const int64_t filled = c.total_bytes / a.ntiles;                        // bytes of a tile on average
     uint32_t from = 16384;
     bool ok = share || rank <= 3;
     switch (a.unit) {
         case 1: case 2:
-            ok = share;
-            from = 12288;
+            ok = share && a.nB == 1 && (out_order || a.nA == 1) && (rank == 2 || filled >= (out_order ? 8192 : 12288));
+            from = 8192;
             break;
         case 4:
-            ok = share ? a.g > 1 || rank == 2 : rank == 3 && pitches % 1024 == 0;
+            ok = share ? rows_gain : rank == 3 && pitches % 1024 == 0;
+            if (share) from = 10240;
             break;
         case 8:
-            from = !share && pitches % 2048 == 0 ? 24576 : 65536;
+            if (share) ok = rows_gain;
+            from = share ? (out_order && a.g == 1 ? 24576 : 10240) : pitches % 2048 == 0 ? 24576 : 65536;
             break;
         default:
-            from = share ? 16384 : pitches % 2048 == 0 ? 24576 : 32768;
+            from = share ? 10240 : pitches % 2048 == 0 ? 24576 : 32768;
             break;
     }
     return ok && a.ntiles >= from ? TF_FOUR_PER_CU : 0;
@@ -856,17 +871,16 @@ static bool diag_by_default(const Canon& c) {
 // its end the next one along the slower axes; where those are in the tile, the end is
 // shared with the tile itself but for its last row.  d tiles apart, a line is gone with
 // d^2 / (d^2 + near^2); a line written in two parts counts `twice` times one read
-// twice.  Both numbers are fitted, on 3000 random shapes of 4 MB to 1 GB, 1- to 16-byte
-// elements, timed in both orders: 64 tiles (128 for 1- and 2-byte units of three axes
-// and more), 1.5 for 1- and 2-byte units and 3 for wider ones, whose rows are longer.
-// Going by this cost where the orders differ by WALK_MARGIN and by element size
-// elsewhere ran 1.044x as fast in geometric mean as element size alone (up to 2.15x);
-// 14 of the shapes ran more than 2.5 % slower (0.70x at worst).  The distance along
-// the fastest axis alone, which the order went by before, left 115 of them.
-constexpr double WALK_MARGIN = 0.1;
-static double walk_cost(const Canon& c, int U, const int* pm, const bool* inA, const bool* inB, const int64_t* t,
+// twice.  Both numbers are fitted on 3000 random shapes of 50 MB to 1 GB, 1- to 16-byte
+// elements, timed in both orders at eight and at four workgroups per CU: 64 tiles, and
+// 1.5 times on small grids, where eight stay, 3 times above (tile_reserve).  The order
+// and the number that go by both rules run 1.010x as long as the best of the four in
+// geometric mean (25 of the shapes more than 1.15x, 1.3x at worst); output order
+// everywhere at four 1.03 to 1.1x and at eight 1.05 to 1.18x, input order 1.13 to 1.3x.
+// Where the orders differ by less than WALK_MARGIN the one by element size stays.
+constexpr double WALK_MARGIN = 0.05;
+static double walk_cost(const Canon& c, const int* pm, const bool* inA, const bool* inB, const int64_t* t,
                         const int64_t* n, uint64_t src, uint64_t dst, bool by_out) {
-    const double near = U <= 2 && c.rank > 2 ? 128.0 : 64.0, twice = U <= 2 ? 1.5 : 3.0;
     const int r = c.rank;
     int64_t stride[MAXR];   // tiles from one along an axis to the next
     int64_t acc = 1;
@@ -875,6 +889,7 @@ static double walk_cost(const Canon& c, int U, const int* pm, const bool* inA, c
         stride[s] = acc;
         acc *= n[s];
     }
+    const double near = 64.0, twice = acc < 8192 ? 1.5 : 3.0;
     auto gone = [&](int64_t d) {
         const double q = (double)d * (double)d;
         return q / (q + near * near);
@@ -1270,8 +1285,8 @@ static rr_status plan_tile_as(uint64_t dst, uint64_t src, const Canon& c, const 
     if (opt.order_out < 0 && (a.flags & TF_XCD)) {
         int64_t n[MAXR];
         for (int s = 0; s < r; ++s) n[s] = tiles_along(s);
-        const double in_first = walk_cost(c, U, pm, inA, inB, t, n, src, dst, false);
-        const double out_first = walk_cost(c, U, pm, inA, inB, t, n, src, dst, true);
+        const double in_first = walk_cost(c, pm, inA, inB, t, n, src, dst, false);
+        const double out_first = walk_cost(c, pm, inA, inB, t, n, src, dst, true);
         const double gain = in_first - out_first;
         if (gain > WALK_MARGIN || gain < -WALK_MARGIN) order_out = gain > 0;
         build_grid(order_out);
@@ -1280,7 +1295,7 @@ static rr_status plan_tile_as(uint64_t dst, uint64_t src, const Canon& c, const 
     if (order_out) a.flags |= TF_ORDER_OUT;
     uint64_t pitches = row_starts;
     for (int q = 0; q < r; ++q) if (q != b1) pitches |= (uint64_t)(sout_el[q] * R);
-    a.flags |= tile_reserve(a, r, pitches, opt);
+    a.flags |= tile_reserve(a, c, pm[0] == 0, pitches, opt);
     p->grid = a.ntiles;
     p->bytes = (uint64_t)c.total_bytes;
     return RR_OK;

@@ -581,6 +581,8 @@ RESERVE_CASES = [
     ((8193, 8195), (1, 0), 4, True), ((4096, 4099), (1, 0), 4, False),         # shared lines, two axes; a small grid
     ((345, 292614), (1, 0), 2, True), ((18, 14, 1016, 266), (0, 3, 2, 1), 2, False),
     ((45, 497, 3467), (0, 2, 1), 4, False), ((784, 624, 576), (0, 2, 1), 1, True),
+    ((984, 84, 2258), (2, 0, 1), 1, True), ((986, 31756), (1, 0), 8, True), ((2601, 4099), (1, 0), 16, True),
+    ((34, 70000, 90), (0, 2, 1), 1, False), ((1275, 247, 196), (0, 2, 1), 8, False),   # thin tiles; small transposes
     ((1812, 222, 47, 18), (1, 2, 0, 3), 1, False),                             # elements of several units
     ((33, 236, 122, 92), (3, 1, 0, 2), 2, False),                              # 2-byte tiles under 14 KiB
     ((5296, 8608), (1, 0), 8, False), ((16384, 16384), (1, 0), 8, True),       # 8-byte units: by the grid
@@ -602,7 +604,8 @@ def test_four_workgroups_per_cu_by_grid_and_unit(dims, perm, e, four):
 # (dims, perm, element bytes, tile order): the order measured faster on shapes whose tiles
 # share lines
 ORDER_CASES = [
-    ((468, 166, 5656), (0, 2, 1), 1, "in"), ((96, 144, 6, 48, 80), (2, 4, 3, 0, 1), 2, "in"),
+    ((18078, 5841), (1, 0), 1, "in"), ((90055, 11054), (1, 0), 1, "out"),            # a small grid, a large one
+    ((96, 144, 6, 48, 80), (2, 4, 3, 0, 1), 2, "in"),
     ((45, 14, 46, 1312), (1, 3, 0, 2), 16, "out"), ((27, 645, 52, 60), (1, 3, 0, 2), 16, "out"),
     ((21, 95, 150, 252), (1, 3, 0, 2), 4, "out"), ((102, 5005, 480), (0, 2, 1), 4, "out"),   # rows that end on lines on one side
     ((156, 2748618), (1, 0), 2, "out"), ((2995, 259995), (1, 0), 1, "out"), ((9744, 18176), (1, 0), 2, "out"),
