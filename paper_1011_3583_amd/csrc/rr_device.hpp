@@ -376,12 +376,13 @@ RR_HD void copy_thread(const CopyArgs& a, uint32_t block, uint32_t nblocks, uint
 // (random 4-byte reads of a 1 GiB table 1632 -> 1378 us for 2^26 indices, with as many
 // lines leaving L2; of a 256 MiB one 1594 -> 1312; fewer than 2^20 of 8 bytes up to 5 %
 // slower).  A range walks its lines once and streams them, and so does a wave whose
-// indices ascend in a set of more than 2^20 of a table above the Infinity Cache (LARGE):
-// the lines of a sorted set are not met again.  Sorted sets of 2 to 16 bytes, cached /
-// streamed, us: of a 300 MiB table 300000 7.7-8.4 / 8.8-9.7, 10^6 18.1-20.6 / 19.0-21.6,
-// 1.25 * 10^6 23.7-27.0 / 22.4-25.9; of a 1 GiB one 300000 7.9-8.7 / 9.2-10.2, 10^6
-// 22.0-24.4 / 21.8-24.3, 4 * 10^6 77-91 / 70-85; of tables up to 256 MiB 1.0-1.1x as
-// fast through the caches.
+// indices ascend in a set of more than 2^20 of a table above 112 MiB (LARGE): the lines
+// of a sorted set are met again from one call to the next only where they fill less than
+// half of the Infinity Cache.  Sorted sets of 2 to 16 bytes, cached against streamed:
+// 500000 of any table 0.88-0.94x the time; 1.5 * 10^6 of 96 MiB 0.95x, of 192 MiB
+// 1.04-1.06x, of 250 MiB to 1 GiB 1.06-1.1x; 4 * 10^6 of 48 MiB 0.93-0.97x, of 96 MiB
+// 1.0-1.015x, of 128 MiB to 1 GiB 1.04-1.08x; 16 * 10^6 and more 0.86-0.88x, 0.96-1.02x
+// and 0.97-1.04x.
 // Returns how many indices fell outside the source.
 
 // Keeps the compiler from moving memory accesses across this point.

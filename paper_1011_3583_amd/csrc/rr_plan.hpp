@@ -71,8 +71,10 @@ struct GatherArgs {
     uint32_t k;            // accesses per element (esize / W)
     uint32_t large;        // 1: an index set that the caches do not hold (plan_gather)
 };
-constexpr int64_t GATHER_CACHED_BYTES = 256ll << 20;   // the Infinity Cache
-constexpr int64_t GATHER_CACHED_COUNT = 1ll << 20;     // indices whose lines fill half of it
+// What an index set's table may hold, and how many indices may read it, for its lines
+// to be met again in the 256 MiB Infinity Cache beside the indices and the output.
+constexpr int64_t GATHER_CACHED_BYTES = 112ll << 20;
+constexpr int64_t GATHER_CACHED_COUNT = 1ll << 20;     // 128 MiB of lines
 
 // 2-D stencil over a rows x cols float grid (Sec. III.D).  shape 0 (star):
 // w[0] center, w[k] the four points at distance k along the axes; shape 1
